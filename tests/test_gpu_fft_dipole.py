@@ -107,3 +107,44 @@ def test_fft_mode_rejects_oversized_lattice_and_keeps_the_state():
         e.set_hamiltonian(DIP)
     assert e.energy() == E0 and e.step_path == path0
     assert np.array_equal(e.get_spins(), n0)
+
+
+# Line lengths 32 .. 1024 along a and b (the last size that fits one length
+# and the first that needs the next), one to four planes in the fused column
+# kernel, five planes and the FP64 1024-point columns in the separate ones,
+# and cells of two and three atoms.
+LENGTHS = {
+    "16x17x1": si.simple_cubic(16, 17, 1, periodic=(0, 0, 0)),
+    "33x64x2": si.simple_cubic(33, 64, 2, periodic=(0, 0, 0)),
+    "65x129x1": si.simple_cubic(65, 129, 1, periodic=(0, 0, 0)),
+    "257x20x1": si.simple_cubic(257, 20, 1, periodic=(0, 0, 0)),
+    "9x257x4": si.simple_cubic(9, 257, 4, periodic=(0, 0, 0)),
+    "7x512x3": si.simple_cubic(7, 512, 3, periodic=(0, 0, 0)),
+    "20x18x5": si.simple_cubic(20, 18, 5, periodic=(0, 0, 0)),
+    "honeycomb18x21": si.honeycomb(18, 21),
+    "kagome20x11": si.kagome(20, 11),
+}
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("case", list(LENGTHS))
+def test_fft_dipole_line_lengths(ora, case, precision):
+    """The repository's parity bounds (FP64 1e-12, FP32 1e-5, normwise): a
+    transform of 2^10 points adds about ten roundings to a field whose terms
+    the direct sum also rounds once each."""
+    announce(f"fft dipole lengths {case} {precision}")
+    geo = LENGTHS[case]
+    k = geo.n_basis
+    ham = si.Hamiltonian(mu=(2.0, 1.5, 0.7)[:k], B=(0, 0, 0), K=(0.0,) * k, K_axis=((0, 0, 1),) * k, ddi=SP_DDI_FFT)
+    import paper_1901_11350_amd as pk
+
+    e = pk.Engine(0, precision)
+    e.set_geometry(geo)
+    e.set_hamiltonian(ham)
+    n = si.uniform_sphere(geo.n_sites, 23)
+    e.set_spins(n)
+    got = e.dipole_gradient()
+    s = ora.System(geo, dataclasses.replace(ham, ddi=True))
+    sites = np.unique(np.concatenate([np.random.default_rng(8).choice(geo.n_sites, 200, replace=False),
+                                      [0, geo.n_sites - 1]]))
+    assert_close(got[:, sites], s.dipole_gradient_sites(n, sites), precision, what=f"FFT dipole {case}")
