@@ -445,6 +445,11 @@ int fft_field(sp_engine* e, const void* n, void* gdd);
 template <typename T>
 int fft_setup(sp_engine* e);
 int fft_check(sp_engine* e);
+template <typename T>
+int fft_step(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout);
+template <typename T>
+bool fft_step_ready(const sp_engine* e);
+void fft_chain(sp_engine* e, bool on);
 
 // Dipole gradient for the step/gradient/observe paths: the direct sum, the
 // FFT convolution, or the learned surrogate with its residual check and
@@ -1236,6 +1241,7 @@ int launch_step(sp_engine* e, const sp_llg_params* p, uint64_t step, const void*
         HIPCHK(e, hipGetLastError());
         return SP_OK;
     }
+    if (fft_step_ready<T>(e)) return fft_step<T>(e, p, step, nin, nout);
     const sp::Lattice L = make_lattice(e);
     const sp::BondCoef<T> C = make_coef<T>(e);
     const sp::Phys<T> P = make_phys<T>(e, p);
@@ -1604,18 +1610,26 @@ int run_impl(sp_engine* e, const sp_llg_params* p, int64_t n_steps, int64_t obse
             if (observe_every > 0) ++k;
         }
     }
+    fft_chain(e, true);
     for (; !persist && t < n_steps; ++t) {
         rc = launch_step<T>(e, p, e->step, e->d_n, e->d_n2);
-        if (rc) return rc;
+        if (rc) {
+            fft_chain(e, false);
+            return rc;
+        }
         std::swap(e->d_n, e->d_n2);
         ++e->step;
         if (observe_every > 0 && (t + 1) % observe_every == 0) {
             rc = launch_observe<T>(e, e->d_n, e->d_obs + k * sp::OBS_NVALS, (long long)e->step, true, nullptr, 0,
                                    tol);
-            if (rc) return rc;
+            if (rc) {
+                fft_chain(e, false);
+                return rc;
+            }
             ++k;
         }
     }
+    fft_chain(e, false);
     int flag = 0;
     long long astep = 0;
     HIPCHK(e, hipMemcpyAsync(&flag, e->d_flag, sizeof(int), hipMemcpyDeviceToHost, e->stream));
