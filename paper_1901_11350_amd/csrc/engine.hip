@@ -139,6 +139,8 @@ struct sp_engine {
     void* d_pos = nullptr;
     void* d_ddpart = nullptr;
     int dd_slices = 1;
+    void* dd_table = nullptr;         // interaction table of the matrix-core direct sum, or null
+    int dd_mslices = 0;               // its slices
     int4* d_bond = nullptr;
     int* d_bstart = nullptr;
     void* d_J = nullptr;
@@ -214,6 +216,7 @@ void free_state_buffers(sp_engine* e) {
     drop_graphs(e);
     dfree(e->d_n); dfree(e->d_n2); dfree(e->d_np); dfree(e->d_A); dfree(e->d_g);
     dfree(e->d_gdd); dfree(e->d_gddp); dfree(e->d_pos); dfree(e->d_ddpart);
+    dfree(e->dd_table);
     void* p = e->d_bond; dfree(p); e->d_bond = nullptr;
     p = e->d_bstart; dfree(p); e->d_bstart = nullptr;
     dfree(e->d_J); dfree(e->d_D); dfree(e->d_J64); dfree(e->d_D64);
@@ -369,22 +372,12 @@ inline unsigned blocks_for(long long n, int bs = 256) { return (unsigned)((n + b
 
 // ----------------------------------------------------------------- dipole
 template <typename T>
+int launch_direct_sum_into(sp_engine* e, const void* n, void* gdd, void* part, const int* gate,
+                           bool vector_form = false);
+
+template <typename T>
 int launch_direct_sum(sp_engine* e, const void* n, void* gdd, const int* gate = nullptr) {
-    sp::DipoleArgs<T> a{};
-    a.N = e->N;
-    a.cells = e->geo.n[0] * e->geo.n[1] * e->geo.n[2];
-    a.slices = e->dd_slices;
-    const int tiles = (e->N + 255) / 256;
-    a.slice_len = ((tiles + a.slices - 1) / a.slices) * 256;
-    for (int b = 0; b < e->geo.nb; ++b) a.mu[b] = (T)e->ham.mu[b];
-    constexpr int IPT = 2;
-    dim3 grid((unsigned)((e->N + 256 * IPT - 1) / (256 * IPT)), (unsigned)a.slices);
-    hipLaunchKernelGGL((sp::k_dipole_partial<T, IPT>), grid, dim3(256), 0, e->stream, a,
-                       static_cast<const T*>(e->d_pos), static_cast<const T*>(n), static_cast<T*>(e->d_ddpart), gate);
-    hipLaunchKernelGGL((sp::k_dipole_finish<T>), dim3(blocks_for(3LL * e->N)), dim3(256), 0, e->stream, a,
-                       (T)kCdd, static_cast<const T*>(e->d_ddpart), static_cast<T*>(gdd), gate);
-    HIPCHK(e, hipGetLastError());
-    return SP_OK;
+    return launch_direct_sum_into<T>(e, n, gdd, e->d_ddpart, gate);
 }
 
 // Scratch of sp_dipole_gradient_dev_noalloc: the S slices of partial sums
@@ -416,24 +409,134 @@ void* scratch_for_device(int device) {
     return g_scratch_ptr[device];
 }
 
+// Plan of the direct sum on the matrix cores (kernels_dipole.hpp): the tile
+// shape for the engine's lattice and whether the form is taken.  The padded
+// products cost 9 x 32 cycles (FP32; 9 x 64 in FP64) of a SIMD per 16 x 16 x
+// 4 pairs, 0.28 (0.56) per pair; the vector form 22.4 instructions at about
+// 3.2 cycles per 64 pairs in FP32, 1.1 per pair, and about 8 in FP64 with
+// its square root and division.  So the form pays while at least a quarter
+// (FP64: a tenth) of the padded products are pairs of the sample, and below
+// 5e7 padded products (6 us of the chip's matrix rate) in any case: there
+// both forms wait on latency, and the vector form's 256-source loop is the
+// longer chain (20 x 20 sites, FP32: 33 us).  Measured, vector against
+// matrix form, us per field: film 128 x 128 x 4 2043 / 721, FP64 7428 /
+// 1510; film 64 x 64 x 2 73 / 33, FP64 167 / 49; honeycomb 100 x 100 289 /
+// 223, FP64 926 / 672.  The table is limited to 256 MiB, and the tiles to
+// grids the hardware takes.
+template <typename T>
+bool dipole_mfma_plan(const sp_engine* e, sp::DipoleMfmaArgs<T>& a, int& wa) {
+    const HostGeo& g = e->geo;
+    a = sp::DipoleMfmaArgs<T>{};
+    a.N = e->N;
+    a.Na = g.n[0];
+    a.Nb = g.n[1];
+    a.Nc = g.n[2];
+    a.Nbas = g.nb;
+    const long long P = (long long)g.n[2] * g.nb;
+    a.P = (int)P;
+    const int t16 = (a.Na + 15) / 16;
+    wa = 1;
+    for (int w = 2; w <= 4; ++w)
+        if ((t16 + w - 1) / w * w <= (t16 + wa - 1) / wa * wa) wa = w;
+    a.tiles_a = (t16 + wa - 1) / wa;
+    a.tiles_b = (a.Nb + 15) / 16;
+    a.chunks = (a.Na + sp::kDipChunk - 1) / sp::kDipChunk;
+    a.pad = 16 * wa * a.tiles_a;
+    a.RL = a.pad + sp::kDipChunk * a.chunks + 4;
+    for (int b = 0; b < g.nb; ++b) a.mu[b] = (T)e->ham.mu[b];
+    const double na = a.Na, nb = a.Nb;
+    const double used = na / (16.0 * wa * a.tiles_a) * (na / (16.0 * t16)) * (nb / (16.0 * a.tiles_b)) * (nb / (nb + 15.0));
+    const double noff = (2.0 * g.n[2] - 1) * g.nb * g.nb;
+    const double padded = (double)e->N * (double)e->N / used;
+    if ((used < (sizeof(T) == 4 ? 0.25 : 0.1) && padded > 5e7) || noff > 65535 || 2LL * a.Nb - 1 > 65535 ||
+        noff * (2.0 * nb - 1) * 6.0 * a.RL * sizeof(T) > 268435456.0 ||
+        (double)P * a.chunks * (nb + 15) > 1e9 || (double)a.tiles_a * a.tiles_b * P > 1e9)
+        return false;
+    // about four workgroups per CU, as far as the partial sums stay within
+    // the engine's slices or the static scratch
+    const long long tiles = (long long)a.tiles_a * a.tiles_b * P, units = P * a.chunks * (a.Nb + 15LL);
+    const long long room = (long long)(((size_t)32 << 20) / (3 * (size_t)e->N * sizeof(T)));
+    long long sl = std::min((1024 + tiles - 1) / tiles, units);
+    sl = std::min(sl, std::max<long long>(e->dd_slices, std::min<long long>(room, 64)));
+    a.slices = (int)std::max<long long>(1, sl);
+    return true;
+}
+
+// Slices of partial sums the direct sum writes.
+int dipole_slices(const sp_engine* e) { return e->dd_table ? std::max(e->dd_slices, e->dd_mslices) : e->dd_slices; }
+
+// Tabulates the interaction of the matrix-core form if the lattice takes it
+// (otherwise the engine has no table and sums on the vector ALUs).
+template <typename T>
+int dipole_table_setup(sp_engine* e) {
+    sp::DipoleMfmaArgs<T> a;
+    int wa;
+    dfree(e->dd_table);
+    e->dd_mslices = 0;
+    if (!dipole_mfma_plan<T>(e, a, wa)) return SP_OK;
+    const HostGeo& g = e->geo;
+    const int noff = (2 * g.n[2] - 1) * g.nb * g.nb;
+    std::vector<double> geo(9 + 3 * (size_t)g.nb);
+    for (int k = 0; k < 9; ++k) geo[k] = g.bravais[k] * g.a;
+    for (int b = 0; b < g.nb; ++b)
+        for (int k = 0; k < 3; ++k) geo[9 + 3 * b + k] = g.basis[3 * b + k] * g.a;
+    double* d_geo = nullptr;
+    int rc = dalloc(e, d_geo, geo.size() * sizeof(double));
+    if (rc) return rc;
+    rc = dalloc(e, e->dd_table, (size_t)noff * (2 * a.Nb - 1) * 6 * a.RL * sizeof(T));
+    if (rc) {
+        (void)hipFree(d_geo);
+        return rc;
+    }
+    hipError_t st = hipMemcpy(d_geo, geo.data(), geo.size() * sizeof(double), hipMemcpyHostToDevice);
+    if (st == hipSuccess) {
+        hipLaunchKernelGGL((sp::k_dipole_table<T>), dim3(blocks_for(a.RL), (unsigned)(2 * a.Nb - 1), (unsigned)noff),
+                           dim3(256), 0, e->stream, a, d_geo, static_cast<T*>(e->dd_table));
+        st = hipGetLastError();
+    }
+    if (st == hipSuccess) st = hipStreamSynchronize(e->stream);
+    (void)hipFree(d_geo);
+    if (st != hipSuccess) return fail(e, SP_E_HIP, std::string("dipole table: ") + hipGetErrorString(st));
+    e->dd_mslices = a.slices;
+    return SP_OK;
+}
+
 // The direct sum with its partials in `part` (the engine's buffer or the
 // static scratch); the partial kernel writes every element of the
-// slices * 3N values before the finish kernel reads them.
+// slices * 3N values before the finish kernel reads them.  vector_form: the
+// form without a table whatever the lattice.
 template <typename T>
-int launch_direct_sum_into(sp_engine* e, const void* n, void* gdd, void* part) {
+int launch_direct_sum_into(sp_engine* e, const void* n, void* gdd, void* part, const int* gate, bool vector_form) {
+    const bool table = e->dd_table && !vector_form;
     sp::DipoleArgs<T> a{};
     a.N = e->N;
     a.cells = e->geo.n[0] * e->geo.n[1] * e->geo.n[2];
-    a.slices = e->dd_slices;
+    a.slices = table ? e->dd_mslices : e->dd_slices;
     const int tiles = (e->N + 255) / 256;
     a.slice_len = ((tiles + a.slices - 1) / a.slices) * 256;
     for (int b = 0; b < e->geo.nb; ++b) a.mu[b] = (T)e->ham.mu[b];
-    constexpr int IPT = 2;
-    dim3 grid((unsigned)((e->N + 256 * IPT - 1) / (256 * IPT)), (unsigned)a.slices);
-    hipLaunchKernelGGL((sp::k_dipole_partial<T, IPT>), grid, dim3(256), 0, e->stream, a,
-                       static_cast<const T*>(e->d_pos), static_cast<const T*>(n), static_cast<T*>(part), nullptr);
+    if (table) {
+        sp::DipoleMfmaArgs<T> m;
+        int wa;
+        (void)dipole_mfma_plan<T>(e, m, wa);
+        const dim3 grid((unsigned)(m.tiles_a * m.tiles_b * m.P), (unsigned)m.slices);
+        const T* K = static_cast<const T*>(e->dd_table);
+        const T* x = static_cast<const T*>(n);
+        T* o = static_cast<T*>(part);
+        switch (wa) {
+            case 1: hipLaunchKernelGGL((sp::k_dipole_mfma<T, 1>), grid, dim3(64), 0, e->stream, m, K, x, o, gate); break;
+            case 2: hipLaunchKernelGGL((sp::k_dipole_mfma<T, 2>), grid, dim3(128), 0, e->stream, m, K, x, o, gate); break;
+            case 3: hipLaunchKernelGGL((sp::k_dipole_mfma<T, 3>), grid, dim3(192), 0, e->stream, m, K, x, o, gate); break;
+            default: hipLaunchKernelGGL((sp::k_dipole_mfma<T, 4>), grid, dim3(256), 0, e->stream, m, K, x, o, gate);
+        }
+    } else {
+        constexpr int IPT = 2;
+        dim3 grid((unsigned)((e->N + 256 * IPT - 1) / (256 * IPT)), (unsigned)a.slices);
+        hipLaunchKernelGGL((sp::k_dipole_partial<T, IPT>), grid, dim3(256), 0, e->stream, a,
+                           static_cast<const T*>(e->d_pos), static_cast<const T*>(n), static_cast<T*>(part), gate);
+    }
     hipLaunchKernelGGL((sp::k_dipole_finish<T>), dim3(blocks_for(3LL * e->N)), dim3(256), 0, e->stream, a,
-                       (T)kCdd, static_cast<const T*>(part), static_cast<T*>(gdd), nullptr);
+                       (T)kCdd, static_cast<const T*>(part), static_cast<T*>(gdd), gate);
     HIPCHK(e, hipGetLastError());
     return SP_OK;
 }
@@ -2082,7 +2185,8 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
         e->dd_slices = std::max(1, std::min(16, (2048 * 256 * 2) / std::max(e->N, 1)));
         e->dd_slices = std::min(e->dd_slices, tiles);
         if ((rc = dalloc(e, e->d_gdd, vbytes)) || (rc = dalloc(e, e->d_gddp, vbytes)) ||
-            (rc = dalloc(e, e->d_ddpart, vbytes * e->dd_slices))) {
+            (rc = DISPATCH(e, dipole_table_setup, e)) ||
+            (rc = dalloc(e, e->d_ddpart, vbytes * dipole_slices(e)))) {
             free_state_buffers(e);
             e->has_ham = false;
             e->has_spins = false;
@@ -2418,7 +2522,7 @@ int sp_dipole_gradient_dev_noalloc(sp_engine* e, const void* n_soa_dev, void* g_
     (void)hipSetDevice(e->device);
     void* part = scratch_for_device(e->device);
     if (!part) return fail(e, SP_E_HIP, "hipGetSymbolAddress of the static scratch failed on this device");
-    return DISPATCH(e, launch_direct_sum_into, e, n_soa_dev, g_soa_dev, part);
+    return DISPATCH(e, launch_direct_sum_into, e, n_soa_dev, g_soa_dev, part, nullptr);
 }
 
 int sp_dipole_gradient(sp_engine* e, double* g_soa, int64_t N) {
