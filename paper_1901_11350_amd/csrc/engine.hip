@@ -30,6 +30,7 @@
 #include "kernels_fused3d.hpp"
 #include "kernels_persist2d.hpp"
 #include "kernels_stencil.hpp"
+#include "kernels_pairs.hpp"
 
 namespace {
 
@@ -139,6 +140,11 @@ struct sp_engine {
     void* d_pos = nullptr;
     void* d_ddpart = nullptr;
     int dd_slices = 1;
+    // general path on LDS tiles (kernels_pairs.hpp)
+    bool pair_ok = false;
+    sp::PairTile ptile{};
+    void* d_pairs = nullptr;          // the exchange records, then the DMI records
+    int pair_js[sp::kMaxBasis + 1] = {}, pair_ds[sp::kMaxBasis + 1] = {};
     void* dd_table = nullptr;         // interaction table of the matrix-core direct sum, or null
     int dd_mslices = 0;               // its slices
     int4* d_bond = nullptr;
@@ -216,7 +222,7 @@ void free_state_buffers(sp_engine* e) {
     drop_graphs(e);
     dfree(e->d_n); dfree(e->d_n2); dfree(e->d_np); dfree(e->d_A); dfree(e->d_g);
     dfree(e->d_gdd); dfree(e->d_gddp); dfree(e->d_pos); dfree(e->d_ddpart);
-    dfree(e->dd_table);
+    dfree(e->dd_table); dfree(e->d_pairs);
     void* p = e->d_bond; dfree(p); e->d_bond = nullptr;
     p = e->d_bstart; dfree(p); e->d_bstart = nullptr;
     dfree(e->d_J); dfree(e->d_D); dfree(e->d_J64); dfree(e->d_D64);
@@ -564,6 +570,141 @@ int launch_dipole(sp_engine* e, const void* n, void* gdd) {
     return launch_direct_sum<T>(e, n, gdd);
 }
 
+// ------------------------------------------------ general path on LDS tiles
+// Plans the tiles of kernels_pairs.hpp for the engine's bond table and
+// uploads its records.  Of the power-of-two shapes of 256 cells the one with
+// the least estimated work is taken: about 25 instructions per staged cell
+// and 5 per bond and site, times the workgroups that LDS leaves short of four
+// per CU.  The form is left to the site loop when no frame fits, or when
+// staging would move more cells than the bonds read (a few bonds of long
+// reach).
+template <typename T>
+int pair_setup(sp_engine* e) {
+    e->pair_ok = false;
+    dfree(e->d_pairs);
+    const HostGeo& g = e->geo;
+    const int nb = g.nb;
+    std::vector<HostBond> bonds;     // offsets of periodic axes reduced to the nearest image
+    std::vector<int> start(nb + 1, 0);
+    int reach[3] = {0, 0, 0};
+    for (int beta = 0; beta < nb; ++beta) {
+        start[beta] = (int)bonds.size();
+        for (int q = e->bstart[beta]; q < e->bstart[beta + 1]; ++q) {
+            HostBond b = e->bonds[q];
+            bool out = false;
+            for (int k = 0; k < 3; ++k) {
+                const int n = g.n[k];
+                if (g.per[k]) {
+                    int d = ((b.d[k] % n) + n) % n;
+                    b.d[k] = d > n / 2 ? d - n : d;
+                } else if (std::abs(b.d[k]) >= n) {
+                    out = true;      // no site has this partner
+                }
+            }
+            if (out || (b.bj == beta && b.d[0] == 0 && b.d[1] == 0 && b.d[2] == 0)) continue;
+            for (int k = 0; k < 3; ++k) reach[k] = std::max(reach[k], std::abs(b.d[k]));
+            bonds.push_back(b);
+        }
+    }
+    start[nb] = (int)bonds.size();
+    sp::PairTile best{};
+    double best_cost = 0.0;
+    for (int lx = 3; lx <= 8; ++lx)
+        for (int ly = 0; lx + ly <= 8; ++ly) {
+            const int lz = 8 - lx - ly;
+            const long long W = (1 << lx) + 2LL * reach[0], H = (1 << ly) + 2LL * reach[1], D = (1 << lz) + 2LL * reach[2];
+            const double bytes = (double)W * H * D * nb * sizeof(sp::V4<T>);
+            if (bytes > 150.0 * 1024) continue;
+            const long long nx = (g.n[0] + (1LL << lx) - 1) >> lx, ny = (g.n[1] + (1LL << ly) - 1) >> ly,
+                            nz = (g.n[2] + (1LL << lz) - 1) >> lz;
+            if (nx * ny * nz > (1LL << 30)) continue;
+            const double groups = std::floor(160.0 * 1024 / bytes);
+            const double cost = (double)(nx * ny * nz) * (25.0 * W * H * D * nb + 5.0 * sp::kPairCells * (double)bonds.size()) *
+                                std::max(1.0, 4.0 / groups);
+            if (best_cost > 0.0 && cost >= best_cost) continue;
+            best_cost = cost;
+            best = sp::PairTile{};
+            best.log_tx = lx;
+            best.log_ty = ly;
+            best.log_tz = lz;
+            best.W = (int)W;
+            best.H = (int)H;
+            best.PN = (int)(W * H * D);
+            best.ra = reach[0];
+            best.rb = reach[1];
+            best.rc = reach[2];
+            best.nx = (int)nx;
+            best.ny = (int)ny;
+            best.nz = (int)nz;
+        }
+    if (best_cost == 0.0 || (double)best.PN * nb > 128.0 * (double)bonds.size() + 2048.0) return SP_OK;
+    auto magic = [](int x) { return (uint32_t)(((1ull << 32) + (uint64_t)x - 1) / (uint64_t)x); };
+    best.magic_PN = magic(best.PN);
+    best.magic_WH = magic(best.W * best.H);
+    best.magic_W = magic(best.W);
+    std::vector<sp::PairJ<T>> J;
+    std::vector<sp::PairD<T>> D;
+    for (int beta = 0; beta < nb; ++beta) {
+        e->pair_js[beta] = (int)J.size();
+        e->pair_ds[beta] = (int)D.size();
+        for (int q = start[beta]; q < start[beta + 1]; ++q) {
+            const HostBond& b = bonds[q];
+            const int off = best.PN * (b.bj - beta) + b.d[0] + best.W * (b.d[1] + best.H * b.d[2]);
+            if (b.J != 0.0) J.push_back(sp::PairJ<T>{off, (T)b.J});
+            if (b.D[0] != 0.0 || b.D[1] != 0.0 || b.D[2] != 0.0)
+                D.push_back(sp::PairD<T>{off, (T)b.D[0], (T)b.D[1], (T)b.D[2]});
+        }
+        while (J.size() % 8) J.push_back(sp::PairJ<T>{0, T(0)});
+        while (D.size() % 4) D.push_back(sp::PairD<T>{0, T(0), T(0), T(0)});
+    }
+    e->pair_js[nb] = (int)J.size();
+    e->pair_ds[nb] = (int)D.size();
+    // division of frame indices by W, W H and PN through a multiplication is
+    // exact below 2^16 (150 KB of LDS hold 9,600 cells)
+    const size_t jb = J.size() * sizeof(J[0]), db = D.size() * sizeof(D[0]);
+    int rc = dalloc(e, e->d_pairs, std::max<size_t>(jb + db, 64));
+    if (rc) return rc;
+    if (jb) HIPCHK(e, hipMemcpy(e->d_pairs, J.data(), jb, hipMemcpyHostToDevice));
+    if (db) HIPCHK(e, hipMemcpy(static_cast<char*>(e->d_pairs) + jb, D.data(), db, hipMemcpyHostToDevice));
+    const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>));
+    if (bytes > 48 * 1024) {
+        const void* fn[] = {(const void*)sp::k_pair_tile<T, sp::PAIR_GRADIENT>, (const void*)sp::k_pair_tile<T, sp::PAIR_PREDICT>,
+                            (const void*)sp::k_pair_tile<T, sp::PAIR_CORRECT>, (const void*)sp::k_pair_tile<T, sp::PAIR_OBSERVE>};
+        for (const void* f : fn)
+            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                return SP_OK;      // the site loop stays
+            }
+    }
+    e->ptile = best;
+    e->pair_ok = true;
+    return SP_OK;
+}
+
+// One launch of the tile kernel; returns its workgroups (rows of partials).
+template <typename T, int STAGE>
+int launch_pair(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* m, const void* n, const void* gdd,
+                void* out) {
+    const sp::PairTile& t = e->ptile;
+    const int tiles = t.nx * t.ny * t.nz;
+    const int grid = STAGE == sp::PAIR_OBSERVE ? std::min(tiles, e->partial_rows) : tiles;
+    sp::PairLists<T> S{};
+    S.j = static_cast<const sp::PairJ<T>*>(e->d_pairs);
+    S.d = reinterpret_cast<const sp::PairD<T>*>(S.j + e->pair_js[e->geo.nb]);
+    for (int b = 0; b <= e->geo.nb; ++b) {
+        S.js[b] = e->pair_js[b];
+        S.ds[b] = e->pair_ds[b];
+    }
+    sp::LLGArgs<T> A{};
+    if (p) A = make_step_llg<T>(e, p, step);
+    hipLaunchKernelGGL((sp::k_pair_tile<T, STAGE>), dim3((unsigned)grid), dim3(sp::kPairCells),
+                       (size_t)t.PN * e->geo.nb * sizeof(sp::V4<T>), e->stream, make_lattice(e), t, S,
+                       make_phys<T>(e, p), A, p ? (int)p->solver : 0, e->d_flag, static_cast<const T*>(m),
+                       static_cast<const T*>(n), static_cast<const T*>(gdd), static_cast<T*>(e->d_A),
+                       static_cast<T*>(out), e->d_partials, tiles);
+    return grid;
+}
+
 // --------------------------------------------------------------- observe
 template <typename T>
 sp::Site2D<T> make_site2d(const sp_engine* e, const sp_llg_params* p);
@@ -649,11 +790,14 @@ int launch_observe(sp_engine* e, const void* n, double* out, long long step, boo
         if (rc) return rc;
         gdd = e->d_gdd;
     }
-    const sp::Phys<T> P = make_phys<T>(e, nullptr);
-    hipLaunchKernelGGL((sp::k_observe_partial<T>), dim3(e->partial_rows), dim3(256), 0, e->stream,
-                       make_lattice(e), make_coef<T>(e), P, static_cast<const T*>(n), static_cast<const T*>(gdd),
-                       e->d_partials);
-    hipLaunchKernelGGL(sp::k_observe_final, dim3(1), dim3(256), 0, e->stream, e->d_partials, e->partial_rows, out,
+    int rows = e->partial_rows;
+    if (e->pair_ok)
+        rows = launch_pair<T, sp::PAIR_OBSERVE>(e, nullptr, 0, n, nullptr, gdd, nullptr);
+    else
+        hipLaunchKernelGGL((sp::k_observe_partial<T>), dim3(e->partial_rows), dim3(256), 0, e->stream,
+                           make_lattice(e), make_coef<T>(e), make_phys<T>(e, nullptr), static_cast<const T*>(n),
+                           static_cast<const T*>(gdd), e->d_partials);
+    hipLaunchKernelGGL(sp::k_observe_final, dim3(1), dim3(256), 0, e->stream, e->d_partials, rows, out,
                        with_flag ? e->d_flag : nullptr, e->d_abort_step, step, step_dev, step_off, tol);
     HIPCHK(e, hipGetLastError());
     return SP_OK;
@@ -1357,7 +1501,9 @@ int launch_step(sp_engine* e, const sp_llg_params* p, uint64_t step, const void*
         gdd = e->d_gdd;
     }
     const dim3 grid(blocks_for(e->N)), block(256);
-    if (p->solver == SP_SOLVER_HEUN)
+    if (e->pair_ok)
+        launch_pair<T, sp::PAIR_PREDICT>(e, p, step, nin, nin, gdd, e->d_np);
+    else if (p->solver == SP_SOLVER_HEUN)
         hipLaunchKernelGGL((sp::k_predict<T, sp::SOLVER_HEUN>), grid, block, 0, e->stream, L, C, P, A, e->d_flag,
                            static_cast<const T*>(nin), static_cast<const T*>(gdd), static_cast<T*>(e->d_np),
                            static_cast<T*>(e->d_A));
@@ -1376,7 +1522,9 @@ int launch_step(sp_engine* e, const sp_llg_params* p, uint64_t step, const void*
         if (rc) return rc;
         gddp = e->d_gddp;
     }
-    if (p->solver == SP_SOLVER_HEUN)
+    if (e->pair_ok)
+        launch_pair<T, sp::PAIR_CORRECT>(e, p, step, e->d_np, nin, gddp, nout);
+    else if (p->solver == SP_SOLVER_HEUN)
         hipLaunchKernelGGL((sp::k_correct<T, sp::SOLVER_HEUN>), grid, block, 0, e->stream, L, C, P, A, e->d_flag,
                            static_cast<const T*>(nin), static_cast<const T*>(e->d_np), static_cast<const T*>(gddp),
                            static_cast<const T*>(e->d_A), static_cast<T*>(nout));
@@ -1564,9 +1712,12 @@ int gradient_dev(sp_engine* e, const void* n, void* g) {
         if (rc) return rc;
         gdd = e->d_gdd;
     }
-    hipLaunchKernelGGL((sp::k_gradient<T>), dim3(blocks_for(e->N)), dim3(256), 0, e->stream, make_lattice(e),
-                       make_coef<T>(e), make_phys<T>(e, nullptr), static_cast<const T*>(n),
-                       static_cast<const T*>(gdd), static_cast<T*>(g));
+    if (e->pair_ok)
+        launch_pair<T, sp::PAIR_GRADIENT>(e, nullptr, 0, n, nullptr, gdd, g);
+    else
+        hipLaunchKernelGGL((sp::k_gradient<T>), dim3(blocks_for(e->N)), dim3(256), 0, e->stream, make_lattice(e),
+                           make_coef<T>(e), make_phys<T>(e, nullptr), static_cast<const T*>(n),
+                           static_cast<const T*>(gdd), static_cast<T*>(g));
     HIPCHK(e, hipGetLastError());
     return SP_OK;
 }
@@ -2193,7 +2344,7 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
             return rc;
         }
     }
-    if ((rc = DISPATCH(e, upload_ham, e)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
+    if ((rc = DISPATCH(e, upload_ham, e)) || (rc = DISPATCH(e, pair_setup, e)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
         free_state_buffers(e);
         e->has_ham = false;
         e->has_spins = false;

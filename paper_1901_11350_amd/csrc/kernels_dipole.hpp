@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(256) k_dipole_partial(DipoleArgs<T> a, const T
 // VALU instructions per pair of the other form; the padding to 16 sites and
 // the Nb + 15 row distances of a 16-row block are its overhead.  Film of 128 x
 // 128 x 4 sites: 1.95 ms per field with the vector form, 0.67 ms with this
-// one (88 % of the padded products at the matrix rate), error against 64 bits
+// one (0.55 ms is the matrix rate of its padded products), error against 64 bits
 // 3.2e-7 before and 2.5e-7 now.
 template <typename T>
 struct DipoleMfmaArgs {
