@@ -574,8 +574,8 @@ int launch_dipole(sp_engine* e, const void* n, void* gdd) {
 // Plans the tiles of kernels_pairs.hpp for the engine's bond table and
 // uploads its records.  Of the power-of-two shapes of 256 cells the one with
 // the least estimated work is taken: about 25 instructions per staged cell
-// and 5 per bond and site, times the workgroups that LDS leaves short of four
-// per CU.  The form is left to the site loop when no frame fits, or when
+// and 5 per bond and site (7 where rows of eight cells meet in the LDS banks),
+// times the workgroups that LDS leaves short of four per CU.  The form is left to the site loop when no frame fits, or when
 // staging would move more cells than the bonds read (a few bonds of long
 // reach).
 template <typename T>
@@ -614,12 +614,12 @@ int pair_setup(sp_engine* e) {
             const int lz = 8 - lx - ly;
             const long long W = (1 << lx) + 2LL * reach[0], H = (1 << ly) + 2LL * reach[1], D = (1 << lz) + 2LL * reach[2];
             const double bytes = (double)W * H * D * nb * sizeof(sp::V4<T>);
-            if (bytes > 150.0 * 1024) continue;
+            if (bytes > 140.0 * 1024) continue;
             const long long nx = (g.n[0] + (1LL << lx) - 1) >> lx, ny = (g.n[1] + (1LL << ly) - 1) >> ly,
                             nz = (g.n[2] + (1LL << lz) - 1) >> lz;
             if (nx * ny * nz > (1LL << 30)) continue;
             const double groups = std::floor(160.0 * 1024 / bytes);
-            const double cost = (double)(nx * ny * nz) * (25.0 * W * H * D * nb + 5.0 * sp::kPairCells * (double)bonds.size()) *
+            const double cost = (double)(nx * ny * nz) * (25.0 * W * H * D * nb + (lx == 3 ? 7.0 : 5.0) * sp::kPairCells * (double)bonds.size()) *
                                 std::max(1.0, 4.0 / groups);
             if (best_cost > 0.0 && cost >= best_cost) continue;
             best_cost = cost;
@@ -660,13 +660,14 @@ int pair_setup(sp_engine* e) {
     e->pair_js[nb] = (int)J.size();
     e->pair_ds[nb] = (int)D.size();
     // division of frame indices by W, W H and PN through a multiplication is
-    // exact below 2^16 (150 KB of LDS hold 9,600 cells)
+    // exact below 2^16 (140 KB of LDS hold 8,960 cells)
     const size_t jb = J.size() * sizeof(J[0]), db = D.size() * sizeof(D[0]);
     int rc = dalloc(e, e->d_pairs, std::max<size_t>(jb + db, 64));
     if (rc) return rc;
     if (jb) HIPCHK(e, hipMemcpy(e->d_pairs, J.data(), jb, hipMemcpyHostToDevice));
     if (db) HIPCHK(e, hipMemcpy(static_cast<char*>(e->d_pairs) + jb, D.data(), db, hipMemcpyHostToDevice));
-    const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>));
+    const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>) + jb + db);
+    if (bytes > 158 * 1024) return SP_OK;
     if (bytes > 48 * 1024) {
         const void* fn[] = {(const void*)sp::k_pair_tile<T, sp::PAIR_GRADIENT>, (const void*)sp::k_pair_tile<T, sp::PAIR_PREDICT>,
                             (const void*)sp::k_pair_tile<T, sp::PAIR_CORRECT>, (const void*)sp::k_pair_tile<T, sp::PAIR_OBSERVE>};
@@ -698,7 +699,9 @@ int launch_pair(sp_engine* e, const sp_llg_params* p, uint64_t step, const void*
     sp::LLGArgs<T> A{};
     if (p) A = make_step_llg<T>(e, p, step);
     hipLaunchKernelGGL((sp::k_pair_tile<T, STAGE>), dim3((unsigned)grid), dim3(sp::kPairCells),
-                       (size_t)t.PN * e->geo.nb * sizeof(sp::V4<T>), e->stream, make_lattice(e), t, S,
+                       (size_t)t.PN * e->geo.nb * sizeof(sp::V4<T>) + (size_t)S.js[e->geo.nb] * sizeof(sp::PairJ<T>) +
+                           (size_t)S.ds[e->geo.nb] * sizeof(sp::PairD<T>),
+                       e->stream, make_lattice(e), t, S,
                        make_phys<T>(e, p), A, p ? (int)p->solver : 0, e->d_flag, static_cast<const T*>(m),
                        static_cast<const T*>(n), static_cast<const T*>(gdd), static_cast<T*>(e->d_A),
                        static_cast<T*>(out), e->d_partials, tiles);

@@ -7,9 +7,10 @@
 // cells, wrapped along periodic axes and zero outside open ones, so a bond
 // is one uniform cell offset: read the cell, multiply, add.  The exchange
 // couplings and the DMI vectors are separate lists of (offset, coupling)
-// records read through the scalar cache, eight or four at a time, so a bond
-// without DMI costs three multiply-adds.  The sums run in the order of the
-// bond table.
+// records, staged in LDS too and read as broadcasts (through the scalar cache
+// every 64 bytes of a cold list were a miss of their own, 11 of 21 us), so a
+// bond without DMI costs three multiply-adds.  The sums run in the order of
+// the bond table.
 //
 // What bounds it: LDS reads, 16 bytes per bond and site.  The site loop it
 // replaces on these lattices (k_predict, k_correct, k_gradient,
@@ -53,10 +54,21 @@ struct PairLists {
 
 enum PairStage { PAIR_GRADIENT = 0, PAIR_PREDICT = 1, PAIR_CORRECT = 2, PAIR_OBSERVE = 3 };
 
+// wrap_coord with the usual case, at most one lattice length away, as two
+// selects (the division only for frames wider than the lattice).
+__device__ __forceinline__ int frame_coord(int t, int n, int per, bool& ok) {
+    if (per) {
+        t += t < 0 ? n : 0;
+        t -= t >= n ? n : 0;
+    }
+    if (t >= 0 && t < n) return t;
+    return wrap_coord(t, n, per, ok);
+}
+
 // The field sums of the exchange and DMI lists of one site.
 template <typename T>
-__device__ __forceinline__ void pair_sums(const PairLists<T>& S, int beta, const V4<T>* cells, int c, V3<T>& gj,
-                                          V3<T>& gd) {
+__device__ __forceinline__ void pair_sums(const PairLists<T>& S, const PairJ<T>* sj, const PairD<T>* sd, int beta,
+                                          const V4<T>* cells, int c, V3<T>& gj, V3<T>& gd) {
     gj = gd = V3<T>{T(0), T(0), T(0)};
     const int j1 = S.js[beta + 1];
     for (int q = S.js[beta]; q < j1; q += 8) {
@@ -64,8 +76,9 @@ __device__ __forceinline__ void pair_sums(const PairLists<T>& S, int beta, const
         T J[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            J[u] = S.j[q + u].J;
-            v[u] = lds_cell_xyz(cells, c + S.j[q + u].off);
+            const PairJ<T> r = sj[q + u];
+            J[u] = r.J;
+            v[u] = lds_cell_xyz(cells, c + r.off);
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) gj = gj - J[u] * v[u];
@@ -75,7 +88,7 @@ __device__ __forceinline__ void pair_sums(const PairLists<T>& S, int beta, const
         V3<T> v[4], D[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const PairD<T> r = S.d[q + u];
+            const PairD<T> r = sd[q + u];
             D[u] = V3<T>{r.x, r.y, r.z};
             v[u] = lds_cell_xyz(cells, c + r.off);
         }
@@ -97,6 +110,10 @@ __global__ void __launch_bounds__(kPairCells)
     if ((STAGE == PAIR_PREDICT || STAGE == PAIR_CORRECT) && abort_flag && *abort_flag) return;
     extern __shared__ __align__(32) unsigned char pair_smem[];
     V4<T>* cells = reinterpret_cast<V4<T>*>(pair_smem);
+    PairJ<T>* sj = reinterpret_cast<PairJ<T>*>(cells + t.PN * L.nb);
+    PairD<T>* sd = reinterpret_cast<PairD<T>*>(sj + S.js[L.nb]);
+    for (int u = threadIdx.x; u < S.js[L.nb]; u += kPairCells) sj[u] = S.j[u];
+    for (int u = threadIdx.x; u < S.ds[L.nb]; u += kPairCells) sd[u] = S.d[u];
     LLGArgs<T> A = A_arg;
     if constexpr (STAGE == PAIR_PREDICT || STAGE == PAIR_CORRECT) A = resolve_step(A_arg);
     const int tid = threadIdx.x;
@@ -125,9 +142,9 @@ __global__ void __launch_bounds__(kPairCells)
                     const int fz = (int)__umulhi((uint32_t)r, t.magic_WH), rr = r - fz * t.W * t.H;
                     const int fy = (int)__umulhi((uint32_t)rr, t.magic_W), fx = rr - fy * t.W;
                     bool ok = true;
-                    const int gx = wrap_coord(x0 - t.ra + fx, na, L.per[0], ok);
-                    const int gy = wrap_coord(y0 - t.rb + fy, nb, L.per[1], ok);
-                    const int gz = wrap_coord(z0 - t.rc + fz, nc, L.per[2], ok);
+                    const int gx = frame_coord(x0 - t.ra + fx, na, L.per[0], ok);
+                    const int gy = frame_coord(y0 - t.rb + fy, nb, L.per[1], ok);
+                    const int gz = frame_coord(z0 - t.rc + fz, nc, L.per[2], ok);
                     if (ok) {
                         const V3<T> s = load3(m, N, gx + na * (gy + nb * (gz + nc * beta)));
                         v[k] = V4<T>{s.x, s.y, s.z, T(0)};
@@ -151,7 +168,7 @@ __global__ void __launch_bounds__(kPairCells)
                 const V3<T> ax{P.Kax[beta][0], P.Kax[beta][1], P.Kax[beta][2]};
                 f.k = (-P.K2[beta] * dot(ax, mi)) * ax;
                 f.q = gauss_gradient(P, mi);
-                pair_sums(S, beta, cells, c, f.j, f.d);
+                pair_sums(S, sj, sd, beta, cells, c, f.j, f.d);
                 V3<T> g = total(f);
                 V3<T> gd{T(0), T(0), T(0)};
                 if (gdd) {
