@@ -2888,17 +2888,19 @@ struct BatchRep {
 struct sp_gneb {
     sp_engine* e = nullptr;
     int device = 0;
-    int M = 0, N = 0, nblk = 0;
+    int M = 0, N = 0, nblk = 0, nblk_e = 0;
+    int ipw_t = 1, ipw_f = 1;   // images per workgroup of the tangent and force kernels
     double k = 1.0, dt = 0.1, m = 1.0;
-    void *x = nullptr, *v = nullptr, *F = nullptr, *Fp = nullptr, *g = nullptr, *tau = nullptr;
+    void *x = nullptr, *x2 = nullptr, *F = nullptr, *g = nullptr;   // chain, the chain's other buffer, force, gradient
     double* part = nullptr;  // force partials (v.F, F.F)
-    double* epart = nullptr; // energy partials [M][nblk]
+    double* scale = nullptr; // velocity scale of the iteration
+    double* epart = nullptr; // energy partials [M][nblk_e]
     double* tpart = nullptr; // tangent partials [M][nblk][3]
     double* E = nullptr;    // [M]
     double* s3 = nullptr;   // [3M]: |tau|^2, g.tau, l^2
     double* vf = nullptr;   // [2]
     int* types = nullptr;   // [M] image types (0 normal, 1 climbing, 2 falling)
-    double* fmax = nullptr; // [(M-2) nblk] block maxima of |F_i|^2 (convergence test)
+    double* fmax = nullptr; // block maxima of |F_i|^2 (convergence test)
     int* stop = nullptr;    // [2]: converged flag, iteration that passed
     int64_t iterations = 0;
     sp_batch* batch = nullptr;   // the batch that advances the chain, if attached
@@ -2933,6 +2935,7 @@ struct sp_batch {
     int cfg = 0;
     int chunk = 32;
     hipGraphExec_t gexec = nullptr;
+    const void* g_chain_x = nullptr;   // the chain buffer its captured graph starts from
     hipGraphExec_t gexec_chain = nullptr;     // an attached chain's chunk, launched beside gexec
     int g_parity = -1, g_cfg = -1, g_chunk = -1;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -3139,6 +3142,7 @@ int batch_capture(sp_batch* b) {
         (void)hipGraphDestroy(g);
         if (s != hipSuccess)
             return bfail(b, SP_E_HIP, std::string("chain graph instantiation failed: ") + hipGetErrorString(s));
+        b->g_chain_x = b->gneb->x;
     }
     b->g_parity = b->parity;
     b->g_cfg = b->cfg;
@@ -3150,7 +3154,7 @@ int batch_advance(sp_batch* b, int64_t n_steps, bool use_graph) {
     int64_t left = n_steps;
     while (use_graph && left >= b->chunk) {
         if (!b->gexec || b->g_parity != b->parity || b->g_cfg != b->cfg || b->g_chunk != b->chunk ||
-            (b->gneb != nullptr) != (b->gexec_chain != nullptr)) {
+            (b->gneb != nullptr) != (b->gexec_chain != nullptr) || (b->gneb && b->g_chain_x != b->gneb->x)) {
             int rc = batch_capture(b);
             if (rc) return rc;
         }
@@ -3413,95 +3417,108 @@ int gfail(sp_gneb* G, int code, const std::string& msg) {
 // k_gneb_grad_shape (then tiles and site blocks coincide in number).
 bool gneb_tiles(const sp_gneb* G) {
     const sp_engine* e = G->e;
-    return e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0 && e->geo.n[0] % 64 == 0 && e->geo.n[1] % 4 == 0 &&
-           (long long)(e->geo.n[0] / 64) * (e->geo.n[1] / 4) == G->nblk;
+    return e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0;
+}
+
+sp::GnebDims gneb_dims(const sp_gneb* G) { return sp::GnebDims{G->M, G->N, G->nblk, G->nblk_e}; }
+
+int gneb_groups(int images, int ipw) { return (images + ipw - 1) / ipw; }
+
+// Partials of v.F and F.F.  Up to 2,048 of them every workgroup of the next
+// position step adds them itself (eight per thread, under its loads); more
+// are added by a launch of their own.
+int gneb_parts(const sp_gneb* G) { return G->nblk * gneb_groups(G->M - 2, G->ipw_f); }
+bool gneb_sum_apart(const sp_gneb* G) { return gneb_parts(G) > 2048; }
+
+// Gradient and energies; move: the position step of the interior images
+// first (the endpoints keep what the first evaluation gave).
+template <typename T, int S, int NDMI>
+void gneb_grad_tiles(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
+    sp_engine* e = G->e;
+    const sp::GnebDims d = gneb_dims(G);
+    const sp::ShapeCoef<double> C = shape_coef_for<double, S>(e);
+    const sp::Site2D<double> Q = make_site2d<double>(e, nullptr);
+    const int tiles_x = (e->geo.n[0] + 15) / 16;
+    T* x = static_cast<T*>(G->x);
+    const bool apart = gneb_sum_apart(G);
+    const double* src = apart ? G->vf : G->part;
+    const int parts = apart ? 1 : gneb_parts(G);
+    if (move) {
+        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, true>), dim3(G->nblk_e, G->M - 2), dim3(256), 0, st, d, C,
+                           Q, tiles_x, (T)G->dt, (T)(G->dt * G->dt / (2.0 * G->m)), src, parts, G->scale,
+                           static_cast<const T*>(G->F), x, static_cast<T*>(G->x2), static_cast<T*>(G->g), G->epart, 1,
+                           stop);
+        std::swap(G->x, G->x2);
+    } else {
+        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, false>), dim3(G->nblk_e, G->M), dim3(256), 0, st, d, C, Q,
+                           tiles_x, T(0), T(0), src, 0, G->scale, static_cast<const T*>(G->F), x,
+                           static_cast<T*>(G->x2), static_cast<T*>(G->g), G->epart, 0, stop);
+    }
 }
 
 template <typename T, int S>
-void gneb_grad_shape(sp_gneb* G, hipStream_t st, const int* stop) {
-    sp_engine* e = G->e;
-    const sp::GnebDims d{G->M, G->N, G->nblk};
-    const sp::ShapeCoef<double> C = shape_coef_for<double, S>(e);
-    const sp::Site2D<double> Q = make_site2d<double>(e, nullptr);
-    const int tiles_x = e->geo.n[0] / 64;
-    const T* x = static_cast<const T*>(G->x);
-    T* g = static_cast<T*>(G->g);
-    const dim3 grid((unsigned)G->nblk, (unsigned)G->M);
-    if (e->shape_ndmi)
-        hipLaunchKernelGGL((sp::k_gneb_grad_shape<T, S, sp::ShapeTab<S>::NB0>), grid, dim3(256), 0, st, d, C, Q,
-                           tiles_x, x, g, G->epart, stop);
-    else
-        hipLaunchKernelGGL((sp::k_gneb_grad_shape<T, S, 0>), grid, dim3(256), 0, st, d, C, Q, tiles_x, x, g, G->epart, stop);
+void gneb_grad_shape(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
+    if (G->e->shape_ndmi) gneb_grad_tiles<T, S, sp::ShapeTab<S>::NB0>(G, st, move, stop);
+    else gneb_grad_tiles<T, S, 0>(G, st, move, stop);
 }
 
+// One evaluation of the forces, after the position step when `move` (an
+// iteration: the partials then also hold the velocity that follows).
 template <typename T>
-int gneb_forces(sp_gneb* G, bool update_v, hipStream_t st, const int* stop = nullptr) {
+int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr) {
     sp_engine* e = G->e;
-    const sp::GnebDims d{G->M, G->N, G->nblk};
-    T* x = static_cast<T*>(G->x);
-    T* g = static_cast<T*>(G->g);
-    T* tau = static_cast<T*>(G->tau);
+    const sp::GnebDims d = gneb_dims(G);
+    const bool apart = gneb_sum_apart(G);
     if (gneb_tiles(G)) {
         switch (e->shape) {
-            case sp::SH_SQ1: gneb_grad_shape<T, sp::SH_SQ1>(G, st, stop); break;
-            case sp::SH_SQ2: gneb_grad_shape<T, sp::SH_SQ2>(G, st, stop); break;
-            case sp::SH_SQ3: gneb_grad_shape<T, sp::SH_SQ3>(G, st, stop); break;
-            case sp::SH_TRI1: gneb_grad_shape<T, sp::SH_TRI1>(G, st, stop); break;
-            case sp::SH_TRI2: gneb_grad_shape<T, sp::SH_TRI2>(G, st, stop); break;
-            default: gneb_grad_shape<T, sp::SH_TRI3>(G, st, stop); break;
+            case sp::SH_SQ1: gneb_grad_shape<T, sp::SH_SQ1>(G, st, move, stop); break;
+            case sp::SH_SQ2: gneb_grad_shape<T, sp::SH_SQ2>(G, st, move, stop); break;
+            case sp::SH_SQ3: gneb_grad_shape<T, sp::SH_SQ3>(G, st, move, stop); break;
+            case sp::SH_TRI1: gneb_grad_shape<T, sp::SH_TRI1>(G, st, move, stop); break;
+            case sp::SH_TRI2: gneb_grad_shape<T, sp::SH_TRI2>(G, st, move, stop); break;
+            default: gneb_grad_shape<T, sp::SH_TRI3>(G, st, move, stop); break;
         }
     } else {
-        hipLaunchKernelGGL((sp::k_gneb_grad<T>), dim3(G->nblk, G->M), dim3(256), 0, st, d, make_lattice(e),
-                           make_coef64(e), make_phys<double>(e, nullptr), x, g, G->epart, stop);
+        if (move)
+            hipLaunchKernelGGL((sp::k_gneb_move<T>), dim3(G->nblk, G->M - 2), dim3(256), 0, st, d, (T)G->dt,
+                               (T)(G->dt * G->dt / (2.0 * G->m)), apart ? G->vf : G->part, apart ? 1 : gneb_parts(G),
+                               G->scale, static_cast<const T*>(G->F), static_cast<T*>(G->x), stop);
+        hipLaunchKernelGGL((sp::k_gneb_grad<T>), dim3(G->nblk, move ? G->M - 2 : G->M), dim3(256), 0, st, d,
+                           make_lattice(e), make_coef64(e), make_phys<double>(e, nullptr),
+                           static_cast<const T*>(G->x), static_cast<T*>(G->g), G->epart, move ? 1 : 0, stop);
     }
-    hipLaunchKernelGGL((sp::k_gneb_tangent<T>), dim3(G->nblk, G->M), dim3(256), 0, st, d, x, g, G->epart, G->E, tau,
-                       G->tpart, stop);
-    hipLaunchKernelGGL((sp::k_gneb_force<T>), dim3(G->nblk, G->M - 2), dim3(256), 0, st, d, (T)G->k,
-                       (T)(G->dt / (2.0 * G->m)), update_v ? 1 : 0, x, g, tau, G->tpart, G->s3, G->types,
-                       static_cast<T*>(G->F), static_cast<const T*>(G->Fp), static_cast<T*>(G->v), G->part,
-                       stop ? G->fmax : nullptr, stop);
-    if (update_v)
-        hipLaunchKernelGGL((sp::k_gneb_sum<2>), dim3(1), dim3(256), 0, st, G->part, (G->M - 2) * G->nblk, G->vf,
-                           stop);
-    hipError_t s = hipGetLastError();
-    if (s != hipSuccess) return gfail(G, SP_E_HIP, hipGetErrorString(s));
-    return SP_OK;
-}
-
-template <typename T>
-int gneb_project(sp_gneb* G, hipStream_t st) {
-    const sp::GnebDims d{G->M, G->N, G->nblk};
-    hipLaunchKernelGGL((sp::k_gneb_project<T>), dim3(G->nblk, G->M - 2), dim3(256), 0, st, d, G->vf,
-                       static_cast<T*>(G->v), static_cast<const T*>(G->F), static_cast<T*>(G->Fp));
+    const T* x = static_cast<const T*>(G->x);
+    const T* g = static_cast<const T*>(G->g);
+    hipLaunchKernelGGL((sp::k_gneb_tangent<T>), dim3(G->nblk, gneb_groups(G->M - 1, G->ipw_t)), dim3(256), 0, st, d,
+                       G->ipw_t, x, g, G->epart, G->E, G->tpart, stop);
+    hipLaunchKernelGGL((sp::k_gneb_force<T>), dim3(G->nblk, gneb_groups(G->M - 2, G->ipw_f)), dim3(256), 0, st, d,
+                       G->ipw_f, (T)G->k, (T)(G->dt / (2.0 * G->m)), move ? 1 : 0, G->scale, x, g, G->E, G->tpart,
+                       G->s3, G->types, static_cast<T*>(G->F), G->part, stop ? G->fmax : nullptr, stop);
+    if (apart)
+        hipLaunchKernelGGL((sp::k_gneb_sum<2>), dim3(1), dim3(256), 0, st, G->part, gneb_parts(G), G->vf, stop);
     hipError_t s = hipGetLastError();
     if (s != hipSuccess) return gfail(G, SP_E_HIP, hipGetErrorString(s));
     return SP_OK;
 }
 
 // n_iter velocity-projection iterations enqueued on st (also under graph
-// capture); the iteration counter is the caller's business.
+// capture, where n_iter is even: each iteration swaps the chain's buffers);
+// the iteration counter is the caller's business.
 // With tol > 0 every iteration ends with the convergence test (largest
 // per-spin force of the interior images below tol); once it passes, the
 // launches of the remaining iterations return at once, so the chain is the
 // one whose forces passed, projected as after any run.
 template <typename T>
 int gneb_enqueue(sp_gneb* G, int n_iter, hipStream_t st, double tol) {
-    const sp::GnebDims d{G->M, G->N, G->nblk};
     const int* stop = tol > 0.0 ? G->stop : nullptr;
     if (stop) hipLaunchKernelGGL(sp::k_gneb_clear_stop, dim3(1), dim3(64), 0, st, G->stop, G->stop + 1);
-    // the projection of each iteration is applied by the next move; the
-    // state between calls is always projected (v, F_prev final)
     for (int it = 0; it < n_iter; ++it) {
-        hipLaunchKernelGGL((sp::k_gneb_move<T>), dim3(G->nblk, G->M - 2), dim3(256), 0, st, d, (T)G->dt,
-                           (T)(G->dt * G->dt / (2.0 * G->m)), it > 0 ? 1 : 0, G->vf, static_cast<const T*>(G->F),
-                           static_cast<T*>(G->x), static_cast<T*>(G->v), static_cast<T*>(G->Fp), stop);
         int rc = gneb_forces<T>(G, true, st, stop);
         if (rc) return rc;
         if (stop)
-            hipLaunchKernelGGL(sp::k_gneb_converged, dim3(1), dim3(256), 0, st, G->fmax, (G->M - 2) * G->nblk,
-                               tol * tol, G->stop, G->stop + 1, it);
+            hipLaunchKernelGGL(sp::k_gneb_converged, dim3(1), dim3(256), 0, st, G->fmax, gneb_parts(G), tol * tol,
+                               G->stop, G->stop + 1, it);
     }
-    if (n_iter > 0) return gneb_project<T>(G, st);
     return SP_OK;
 }
 
@@ -3545,7 +3562,7 @@ int gneb_download(sp_gneb* G, const void* src, double* out, size_t count) {
 }
 
 void gneb_free(sp_gneb* G) {
-    void* ps[] = {G->x,  G->v,  G->F,  G->Fp, G->g,     G->tau,  G->part, G->epart,
+    void* ps[] = {G->x,  G->x2, G->F, G->g, G->scale, G->part, G->epart,
                   G->tpart, G->E, G->s3, G->vf, G->types, G->fmax, G->stop};
     for (void* p : ps)
         if (p) (void)hipFree(p);
@@ -3578,16 +3595,22 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
     G->m = vp_mass;
     (void)hipSetDevice(e->device);
     const size_t vb = (size_t)G->M * 3 * G->N * e->esz();
+    // gradient tiles of 16 x 16 sites or blocks of 256; as many images per
+    // workgroup in the other two kernels as leave about 512 workgroups
+    G->nblk_e = gneb_tiles(G) ? ((e->geo.n[0] + 15) / 16) * ((e->geo.n[1] + 15) / 16) : G->nblk;
+    G->ipw_t = (int)std::max<long long>(1, std::min<long long>(sp::kGnebImages, (long long)G->nblk * (G->M - 1) / 512));
+    G->ipw_f = (int)std::max<long long>(1, std::min<long long>(sp::kGnebImages, (long long)G->nblk * (G->M - 2) / 512));
     const size_t parts = (size_t)(G->M - 2) * G->nblk * 2;
-    void** bufs[] = {&G->x, &G->v, &G->F, &G->Fp, &G->g, &G->tau};
+    void** bufs[] = {&G->x, &G->x2, &G->F, &G->g};
     for (void** b : bufs)
         if (hipMalloc(b, vb) != hipSuccess) { gneb_free(G); delete G; return fail(e, SP_E_NOMEM, "GNEB allocation failed"); }
     if (hipMalloc((void**)&G->part, parts * sizeof(double)) != hipSuccess ||
-        hipMalloc((void**)&G->epart, (size_t)G->M * G->nblk * sizeof(double)) != hipSuccess ||
+        hipMalloc((void**)&G->epart, (size_t)G->M * G->nblk_e * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->tpart, (size_t)G->M * G->nblk * 3 * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->E, G->M * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->s3, 3 * G->M * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->vf, 2 * sizeof(double)) != hipSuccess ||
+        hipMalloc((void**)&G->scale, sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->types, G->M * sizeof(int)) != hipSuccess ||
         hipMalloc((void**)&G->fmax, (size_t)(G->M - 2) * G->nblk * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->stop, 2 * sizeof(int)) != hipSuccess) {
@@ -3595,8 +3618,7 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
         delete G;
         return fail(e, SP_E_NOMEM, "GNEB allocation failed");
     }
-    if (hipMemset(G->v, 0, vb) != hipSuccess || hipMemset(G->F, 0, vb) != hipSuccess ||
-        hipMemset(G->Fp, 0, vb) != hipSuccess || hipMemset(G->tau, 0, vb) != hipSuccess ||
+    if (hipMemset(G->F, 0, vb) != hipSuccess || hipMemset(G->scale, 0, sizeof(double)) != hipSuccess ||
         hipMemset(G->vf, 0, 2 * sizeof(double)) != hipSuccess || hipMemset(G->types, 0, G->M * sizeof(int)) != hipSuccess ||
         hipMemset(G->stop, 0, 2 * sizeof(int)) != hipSuccess) {
         gneb_free(G);
@@ -3604,11 +3626,12 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
         return fail(e, SP_E_HIP, "GNEB initialisation failed");
     }
     rc = e->precision == SP_F64 ? gneb_upload<double>(G, chain) : gneb_upload<float>(G, chain);
+    // the endpoints have to stand in both chain buffers
+    if (rc == SP_OK && hipMemcpy(G->x2, G->x, vb, hipMemcpyDeviceToDevice) != hipSuccess)
+        rc = gfail(G, SP_E_HIP, "chain copy failed");
     if (rc == SP_OK)
         rc = e->precision == SP_F64 ? gneb_forces<double>(G, false, e->stream) : gneb_forces<float>(G, false, e->stream);
-    // v = 0 (vf = 0 gives a zero projection) and F_prev = F
-    if (rc == SP_OK)
-        rc = e->precision == SP_F64 ? gneb_project<double>(G, e->stream) : gneb_project<float>(G, e->stream);
+    // v = 0: the evaluation leaves v.F = 0 in the partials
     if (rc == SP_OK && hipStreamSynchronize(e->stream) != hipSuccess) rc = SP_E_HIP;
     if (rc) {
         e->err = G->err;
@@ -3678,6 +3701,8 @@ int sp_gneb_iterate_tol(sp_gneb* G, int max_iter, double tol, int* iters_done) {
          hipStreamSynchronize(G->e->stream) != hipSuccess))
         return gfail(G, SP_E_HIP, "synchronisation failed");
     const int done = st[0] ? st[1] + 1 : max_iter;
+    // the skipped iterations swapped the chain's buffers on the host only
+    if (gneb_tiles(G) && (max_iter - done) % 2) std::swap(G->x, G->x2);
     G->iterations += done;
     if (iters_done) *iters_done = done;
     return SP_OK;
@@ -3704,7 +3729,7 @@ int sp_gneb_get_forces(sp_gneb* G, double* E, double* l, double* F) {
     }
     if (F) {
         const size_t n = (size_t)G->M * 3 * G->N;
-        return G->e->precision == SP_F64 ? gneb_download<double>(G, G->Fp, F, n) : gneb_download<float>(G, G->Fp, F, n);
+        return G->e->precision == SP_F64 ? gneb_download<double>(G, G->F, F, n) : gneb_download<float>(G, G->F, F, n);
     }
     return SP_OK;
 }

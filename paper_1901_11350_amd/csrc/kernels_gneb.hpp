@@ -3,25 +3,35 @@
 // velocity-projection minimiser).
 //
 // The chain holds M images of N spins, image-major, each image SoA.  Images 0
-// and M-1 are fixed.  Per velocity-projection iteration (five launches):
-//   k_gneb_move       [projection of the previous iteration: v <- (v.F/F.F) F
-//                     if v.F > 0 else 0, F_prev <- F]  then
-//                     x <- normalise(x + dt v + dt^2/(2m) F_prev)    (interior)
-//   k_gneb_grad       g = dH/dn per image, energy partials per block
-//                     (k_gneb_grad_shape on the stencil path's tiles)
+// and M-1 are fixed.  Between iterations the minimiser's state is the chain,
+// the force F of the last evaluation and the partials of v.F and F.F: the
+// projected velocity is v = (v.F/F.F) F if v.F > 0 else 0, a multiple of F,
+// so no velocity array exists.  Per velocity-projection iteration:
+//   k_gneb_grad_tile  s = v.F/F.F from the partials, then on tiles of the
+//                     image: x <- normalise(x + dt s F + dt^2/(2m) F) (into
+//                     the other chain buffer), g = dH/dn, energy partials
+//                     (k_gneb_move in place and k_gneb_grad on lattices
+//                     without a compile-time 2D stencil)
 //   k_gneb_tangent    E of the image and its neighbours from the partials;
 //                     improved tangent, per-spin projection; partials of
 //                     |tau|^2, g.tau, and squared geodesic angles to image v+1
-//   k_gneb_force      |tau|^2, g.tau, l^2 from the partials;
+//   k_gneb_force      |tau|^2, g.tau, l^2 from the partials; the tangent
+//                     again (two multiply-adds a component, against storing
+//                     and loading it);
 //                     F = -g + (g.t)t, per-spin projected, + k (l_v - l_{v-1}) t
 //                     (climbing images: -g + 2 (g.t)t, falling: -g, no spring)
-//                     with t = tau/|tau|; v <- v + dt/(2m)(F_prev + F);
-//                     chain-wide partials of v.F and F.F
-//   k_gneb_sum        v.F, F.F
-// k_gneb_project applies the last projection when a run of iterations ends.
+//                     with t = tau/|tau|; partials of v.F and F.F with
+//                     v <- s F_prev + dt/(2m)(F_prev + F)
+// The last two walk several images per workgroup, so a chain's arrays are
+// read about once each; k_gneb_sum adds the partials of large chains, whose
+// every workgroup would otherwise spend its time on them.
 // Every reduction is a fixed-order FP64 tree: a row of partials is summed by
-// the same thread-strided loop and tree in every workgroup that needs it
+// the same strided loop and tree in every workgroup that needs it
 // (bit-reproducible, identical everywhere).
+// What bounds it: about 7 passes over arrays that stay in the last-level
+// cache, and the latency of three dependent launches.  On 32 images of
+// 128^2 spins (FP32) six launches with stored velocity, previous force and
+// tangent took 45 us per iteration.
 #pragma once
 
 #include "kernels_field.hpp"
@@ -46,28 +56,56 @@ __device__ __forceinline__ void block_sums(double* acc) {
     }
 }
 
-// Sum of row `row` of NV-value partials (nblk per row), fixed order; every
-// thread receives the result.
+// Sum of row `row` of NV-value partials (nblk per row) by one wavefront,
+// fixed order; every lane receives the result.
 template <int NV>
-__device__ __forceinline__ void row_sum(const double* __restrict__ part, int nblk, int row, double* out) {
-    double acc[NV];
+__device__ __forceinline__ void wave_row_sum(const double* __restrict__ part, int nblk, int row, double* out) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += 256) {
+    for (int k = 0; k < NV; ++k) out[k] = 0.0;
+    for (int b = threadIdx.x & 63; b < nblk; b += 64) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) acc[k] += part[((size_t)row * nblk + b) * NV + k];
+        for (int k = 0; k < NV; ++k) out[k] += part[((size_t)row * nblk + b) * NV + k];
     }
-    block_sums<NV>(acc);
-    __shared__ double bc[NV];
-    if (threadIdx.x == 0) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) bc[k] = acc[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; ++k) out[k] = bc[k];
-    __syncthreads();
+    for (int k = 0; k < NV; ++k) out[k] = wave_sum(out[k]);
 }
+
+// Velocity scale s = v.F / F.F (0 unless both are positive) from `count`
+// partials; every thread receives it.
+__device__ __forceinline__ double gneb_scale(const double* __restrict__ part, int count) {
+    double acc[2] = {0.0, 0.0};
+    for (int b = threadIdx.x; b < count; b += 256) {
+        acc[0] += part[2 * b];
+        acc[1] += part[2 * b + 1];
+    }
+    block_sums<2>(acc);
+    __shared__ double bc;
+    if (threadIdx.x == 0) bc = acc[0] > 0.0 && acc[1] > 0.0 ? acc[0] / acc[1] : 0.0;
+    __syncthreads();
+    return bc;
+}
+
+// Weights of the improved tangent towards the next and the previous image.
+__device__ __forceinline__ void gneb_weights(double Em, double E0, double Ep, double& wp, double& wm) {
+    if (Ep > E0 && E0 > Em) {
+        wp = 1.0; wm = 0.0;
+    } else if (Ep < E0 && E0 < Em) {
+        wp = 0.0; wm = 1.0;
+    } else {
+        const double d1 = fabs(Ep - E0), d2 = fabs(Em - E0);
+        const double dmax = d1 > d2 ? d1 : d2, dmin = d1 > d2 ? d2 : d1;
+        if (Ep > Em) { wp = dmax; wm = dmin; } else { wp = dmin; wm = dmax; }
+    }
+}
+
+// Tangent of one spin, unnormalised, projected onto its tangent plane.
+template <typename T>
+__device__ __forceinline__ V3<T> gneb_tau(V3<T> nm, V3<T> n0, V3<T> np, double wp, double wm) {
+    const V3<T> t = T(wp) * (np - n0) + T(wm) * (n0 - nm);
+    return t - dot(t, n0) * n0;
+}
+
+constexpr int kGnebImages = 8;    // images per workgroup of the tangent and force kernels, at most
 
 // Maximum over the block (thread 0 receives it).
 __device__ __forceinline__ double block_max(double v) {
@@ -84,42 +122,33 @@ struct GnebDims {
     int M;         // images
     int N;         // spins per image
     int nblk;      // blocks per image in the per-site kernels
+    int nblk_e;    // energy partials per image (blocks of the gradient kernel)
 };
 
+// Position step of one spin: x + dt v + dt^2/(2m) F with v = scale F,
+// renormalised.
 template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_move(GnebDims d, T dt, T half_dt2_m, int project,
-                                                   const double* __restrict__ vf_ff, const T* __restrict__ F,
-                                                   T* __restrict__ x, T* __restrict__ v, T* __restrict__ Fp,
-    const int* __restrict__ stop) {
+__device__ __forceinline__ V3<T> gneb_moved(V3<T> x, V3<T> f, T scale, T dt, T half_dt2_m) {
+    const T n0 = x.x + dt * (scale * f.x) + half_dt2_m * f.x;
+    const T n1 = x.y + dt * (scale * f.y) + half_dt2_m * f.y;
+    const T n2 = x.z + dt * (scale * f.z) + half_dt2_m * f.z;
+    const T r = T(1) / sqrt(n0 * n0 + n1 * n1 + n2 * n2);
+    return V3<T>{n0 * r, n1 * r, n2 * r};
+}
+
+// The position step alone, in place (interior images).
+template <typename T>
+__global__ void __launch_bounds__(256) k_gneb_move(GnebDims d, T dt, T half_dt2_m, const double* __restrict__ part,
+                                                   int parts, double* __restrict__ scale_out,
+                                                   const T* __restrict__ F, T* __restrict__ x,
+                                                   const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
+    const double sc = gneb_scale(part, parts);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *scale_out = sc;
     const int i = blockIdx.x * 256 + threadIdx.x;
-    const int im = blockIdx.y + 1;   // interior images only
     if (i >= d.N) return;
-    const size_t base = (size_t)im * 3 * d.N;
-    T scale = T(0);
-    if (project) {
-        const double vf = vf_ff[0], ff = vf_ff[1];
-        scale = (vf > 0.0 && ff > 0.0) ? (T)(vf / ff) : T(0);
-    }
-    T n[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const size_t q = base + (size_t)c * d.N + i;
-        T vq, fq;
-        if (project) {
-            fq = F[q];
-            vq = scale * fq;
-            v[q] = vq;
-            Fp[q] = fq;
-        } else {
-            vq = v[q];
-            fq = Fp[q];
-        }
-        n[c] = x[q] + dt * vq + half_dt2_m * fq;
-    }
-    const T r = T(1) / sqrt(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) x[base + (size_t)c * d.N + i] = n[c] * r;
+    const size_t off = (size_t)(blockIdx.y + 1) * 3 * d.N;
+    store3(x + off, d.N, i, gneb_moved(load3(x + off, d.N, i), load3(F + off, d.N, i), (T)sc, dt, half_dt2_m));
 }
 
 // Gradient of every image and per-block energy partials (Zeeman linear,
@@ -127,14 +156,14 @@ __global__ void __launch_bounds__(256) k_gneb_move(GnebDims d, T dt, T half_dt2_
 template <typename T>
 __global__ void __launch_bounds__(256) k_gneb_grad(GnebDims d, Lattice L, BondCoef<double> C, Phys<double> P,
                                                    const T* __restrict__ x, T* __restrict__ g,
-                                                   double* __restrict__ part,
-    const int* __restrict__ stop) {
+                                                   double* __restrict__ part, int im0,
+                                                   const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
     // field and energy in FP64 from the stored spins (type T): the image
     // energies decide the tangent's branch, so they are formed in the
     // reference's precision for both engine precisions; g is stored as T
     const int i = blockIdx.x * 256 + threadIdx.x;
-    const int im = blockIdx.y;
+    const int im = im0 + blockIdx.y;
     const T* xi = x + (size_t)im * 3 * d.N;
     double acc[1] = {0.0};
     if (i < d.N) {
@@ -148,62 +177,92 @@ __global__ void __launch_bounds__(256) k_gneb_grad(GnebDims d, Lattice L, BondCo
                  gauss_energy(P, ni);
     }
     block_sums<1>(acc);
-    if (threadIdx.x == 0) part[(size_t)im * d.nblk + blockIdx.x] = acc[0];
+    if (threadIdx.x == 0) part[(size_t)im * d.nblk_e + blockIdx.x] = acc[0];
 }
 
-// The same gradient and energy partials on the stencil path's tiles, for
-// one-atom 2D images with a compile-time stencil whose sides divide into
-// 64 x 4 tiles: tile t of an image (256 sites, one per thread) is partial t
-// of its row, as block t is in k_gneb_grad.  The image is staged in LDS with
-// an R halo as FP64 cells; the terms are those of shape_terms, in FP64 from
-// the stored spins.
-template <typename T, int S, int NDMI>
-__global__ void __launch_bounds__(256) k_gneb_grad_shape(GnebDims d, ShapeCoef<double> C, Site2D<double> Q,
-                                                         int tiles_x, const T* __restrict__ x, T* __restrict__ g,
-                                                         double* __restrict__ part,
-    const int* __restrict__ stop) {
+// The same on 16 x 16 tiles of one-atom 2D images with a compile-time
+// stencil (ragged tiles allowed), after the position step when MOVE: the
+// tile and its R halo are stepped on the way into LDS (FP64 cells) and the
+// tile's own spins stored to the other chain buffer.  16 x 16 has the
+// smallest halo of the 256-site shapes (1.27 and 1.56 times the tile for R =
+// 1 and 2; 64 x 4: 1.55 and 2.1).  The terms are those of shape_terms, in
+// FP64 from the spins as stored.
+template <typename T, int S, int NDMI, bool MOVE>
+__global__ void __launch_bounds__(256)
+    k_gneb_grad_tile(GnebDims d, ShapeCoef<double> C, Site2D<double> Q, int tiles_x, T dt, T half_dt2_m,
+                     const double* __restrict__ fpart, int parts, double* __restrict__ scale_out,
+                     const T* __restrict__ F, const T* __restrict__ x, T* __restrict__ xn, T* __restrict__ g,
+                     double* __restrict__ part, int im0, const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    constexpr int TX = 64, TY = 4, NT = 256;
+    constexpr int TX = 16, TY = 16, NT = 256;
     constexpr int R = ShapeTab<S>::R, W = TX + 2 * R, H = TY + 2 * R, P = W * H, KST = (P + NT - 1) / NT;
     __shared__ V4<double> sN[P];
-    const int im = blockIdx.y, tile = blockIdx.x;
+    const int im = im0 + blockIdx.y, tile = blockIdx.x;
     const int tyi = tile / tiles_x;
     const int x0 = (tile - tyi * tiles_x) * TX, y0 = tyi * TY;
     const int N = d.N, tid = threadIdx.x;
-    const T* xi = x + (size_t)im * 3 * N;
-    V4<double> st[KST];
+    const size_t off = (size_t)im * 3 * N;
+    V3<T> st[KST], sf[KST];
+    int site[KST];               // the cell's site, or -1 outside an open lattice
+    bool own[KST];
 #pragma unroll
     for (int k = 0; k < KST; ++k) {
         const int idx = tid + k * NT;
-        st[k] = V4<double>{0.0, 0.0, 0.0, 0.0};
+        site[k] = -1;
+        own[k] = false;
+        st[k] = sf[k] = V3<T>{T(0), T(0), T(0)};
         if (idx < P) {
             const int ly = idx / W, lx = idx - ly * W;
             bool in = true;
-            const int gx = wrap_once(x0 - R + lx, Q.na, Q.per_a, in);
-            const int gy = wrap_once(y0 - R + ly, Q.nb, Q.per_b, in);
+            const int ux = x0 - R + lx, uy = y0 - R + ly;
+            const int gx = wrap_once(ux, Q.na, Q.per_a, in);
+            const int gy = wrap_once(uy, Q.nb, Q.per_b, in);
             if (in) {
-                const int q = gx + gy * Q.na;
-                st[k] = V4<double>{(double)xi[q], (double)xi[N + q], (double)xi[2 * N + q], 0.0};
+                site[k] = gx + gy * Q.na;
+                own[k] = lx >= R && lx < R + TX && ly >= R && ly < R + TY && ux < Q.na && uy < Q.nb;
+                st[k] = load3(x + off, N, site[k]);
+                if (MOVE) sf[k] = load3(F + off, N, site[k]);
             }
         }
+    }
+    T scale = T(0);
+    if constexpr (MOVE) {
+        const double sc = gneb_scale(fpart, parts);
+        if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *scale_out = sc;
+        scale = (T)sc;
     }
 #pragma unroll
     for (int k = 0; k < KST; ++k) {
         const int idx = tid + k * NT;
-        if (idx < P) sN[idx] = st[k];
+        if (idx < P) {
+            V4<double> cell{0.0, 0.0, 0.0, 0.0};
+            if (site[k] >= 0) {
+                V3<T> s = st[k];
+                if constexpr (MOVE) {
+                    s = gneb_moved(s, sf[k], scale, dt, half_dt2_m);
+                    if (own[k]) store3(xn + off, N, site[k], s);
+                }
+                cell = V4<double>{(double)s.x, (double)s.y, (double)s.z, 0.0};
+            }
+            sN[idx] = cell;
+        }
     }
     __syncthreads();
     const int ty = tid / TX, tx = tid - ty * TX;
-    const int c = (ty + R) * W + (tx + R);
-    const V3<double> ni = lds_cell_xyz(sN, c);
-    const FieldTerms<double> f = shape_terms<double, S, NDMI, W>(C, Q, sN, c, ni);
-    const V3<double> gt = f.z + f.k + f.j + f.d;
-    store3(g + (size_t)im * 3 * N, N, (x0 + tx) + (y0 + ty) * Q.na, V3<T>{(T)gt.x, (T)gt.y, (T)gt.z});
-    double acc[1] = {ni.x * f.z.x + ni.y * f.z.y + ni.z * f.z.z +
-                     0.5 * (ni.x * (f.k.x + f.j.x + f.d.x) + ni.y * (f.k.y + f.j.y + f.d.y) +
-                            ni.z * (f.k.z + f.j.z + f.d.z))};
+    const int gx = x0 + tx, gy = y0 + ty;
+    double acc[1] = {0.0};
+    if (gx < Q.na && gy < Q.nb) {
+        const int c = (ty + R) * W + (tx + R);
+        const V3<double> ni = lds_cell_xyz(sN, c);
+        const FieldTerms<double> f = shape_terms<double, S, NDMI, W>(C, Q, sN, c, ni);
+        const V3<double> gt = f.z + f.k + f.j + f.d;
+        store3(g + off, N, gx + gy * Q.na, V3<T>{(T)gt.x, (T)gt.y, (T)gt.z});
+        acc[0] = ni.x * f.z.x + ni.y * f.z.y + ni.z * f.z.z +
+                 0.5 * (ni.x * (f.k.x + f.j.x + f.d.x) + ni.y * (f.k.y + f.j.y + f.d.y) +
+                        ni.z * (f.k.z + f.j.z + f.d.z));
+    }
     block_sums<1>(acc);
-    if (tid == 0) part[(size_t)im * d.nblk + tile] = acc[0];
+    if (tid == 0) part[(size_t)im * d.nblk_e + tile] = acc[0];
 }
 
 // Sum NV-value partials of each of `rows` rows (blocks per row = nblk) in a
@@ -227,122 +286,142 @@ __global__ void __launch_bounds__(256) k_gneb_sum(const double* __restrict__ par
     }
 }
 
-// Tangent of interior images (unnormalised, per-spin projected) and partials
-// of |tau|^2, g.tau and the squared great-circle angle to image im+1.
+// Partials of |tau|^2, g.tau (interior images) and of the squared
+// great-circle angle to the next image, for the `ipw` images from
+// blockIdx.y * ipw (images 0 .. M - 2); E of every image.
 template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, const T* __restrict__ x, const T* __restrict__ g,
-                                                      const double* __restrict__ epart, double* __restrict__ E,
-                                                      T* __restrict__ tau, double* __restrict__ part,
-    const int* __restrict__ stop) {
+__global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, int ipw, const T* __restrict__ x,
+                                                      const T* __restrict__ g, const double* __restrict__ epart,
+                                                      double* __restrict__ E, double* __restrict__ part,
+                                                      const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int im = blockIdx.y;
-    // energies of this image and its neighbours
-    double Em = 0.0, E0 = 0.0, Ep = 0.0;
-    row_sum<1>(epart, d.nblk, im, &E0);
-    if (im > 0 && im + 1 < d.M) {
-        row_sum<1>(epart, d.nblk, im - 1, &Em);
-        row_sum<1>(epart, d.nblk, im + 1, &Ep);
+    __shared__ double sE[kGnebImages + 2];
+    __shared__ double red[kGnebImages][3][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = blockIdx.x * 256 + tid;
+    const int im0 = blockIdx.y * ipw, im1 = min(im0 + ipw, d.M - 1);
+    const size_t L3 = (size_t)3 * d.N;
+    const int ic = min(i, d.N - 1);
+    V3<T> nm = load3(x + (size_t)max(im0 - 1, 0) * L3, d.N, ic), n0 = load3(x + im0 * L3, d.N, ic);
+    // energies of images im0 - 1 .. im1
+    for (int r = max(im0 - 1, 0) + wave; r <= im1; r += 4) {
+        double e;
+        wave_row_sum<1>(epart, d.nblk_e, r, &e);
+        if (lane == 0) {
+            sE[r - im0 + 1] = e;
+            if (blockIdx.x == 0 && (r >= im0 && (r < im1 || r == d.M - 1))) E[r] = e;
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) E[im] = E0;
-    double acc[3] = {0.0, 0.0, 0.0};
-    if (i < d.N) {
-        const size_t L3 = (size_t)3 * d.N;
-        const V3<T> n0 = load3(x + im * L3, d.N, i);
-        if (im + 1 < d.M) {
-            const V3<T> n1 = load3(x + (im + 1) * L3, d.N, i);
-            const V3<T> c = cross(n0, n1);
+    __syncthreads();
+    for (int im = im0; im < im1; ++im) {
+        const V3<T> np = load3(x + (im + 1) * L3, d.N, ic);
+        double acc[3] = {0.0, 0.0, 0.0};
+        if (i < d.N) {
+            const V3<T> c = cross(n0, np);
             // angle in working precision (its inputs are), squared sum in FP64
-            const double ang = (double)atan2(sqrt(dot(c, c)), dot(n0, n1));
+            const double ang = (double)atan2(sqrt(dot(c, c)), dot(n0, np));
             acc[2] = ang * ang;
-        }
-        if (im > 0 && im + 1 < d.M) {
-            const V3<T> nm = load3(x + (im - 1) * L3, d.N, i);
-            const V3<T> np = load3(x + (im + 1) * L3, d.N, i);
-            double wp, wm;
-            if (Ep > E0 && E0 > Em) {
-                wp = 1.0; wm = 0.0;
-            } else if (Ep < E0 && E0 < Em) {
-                wp = 0.0; wm = 1.0;
-            } else {
-                const double d1 = fabs(Ep - E0), d2 = fabs(Em - E0);
-                const double dmax = d1 > d2 ? d1 : d2, dmin = d1 > d2 ? d2 : d1;
-                if (Ep > Em) { wp = dmax; wm = dmin; } else { wp = dmin; wm = dmax; }
+            if (im > 0) {
+                double wp, wm;
+                gneb_weights(sE[im - im0], sE[im - im0 + 1], sE[im - im0 + 2], wp, wm);
+                const V3<T> t = gneb_tau(nm, n0, np, wp, wm);
+                const V3<T> gi = load3(g + im * L3, d.N, i);
+                acc[0] = (double)dot(t, t);
+                acc[1] = (double)dot(gi, t);
             }
-            V3<T> t = T(wp) * (np - n0) + T(wm) * (n0 - nm);
-            t = t - dot(t, n0) * n0;
-            store3(tau + im * L3, d.N, i, t);
-            const V3<T> gi = load3(g + im * L3, d.N, i);
-            acc[0] = (double)dot(t, t);
-            acc[1] = (double)dot(gi, t);
         }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double v = wave_sum(acc[k]);
+            if (lane == 0) red[im - im0][k][wave] = v;
+        }
+        nm = n0;
+        n0 = np;
     }
-    block_sums<3>(acc);
-    if (threadIdx.x == 0) {
-        double* o = part + ((size_t)im * d.nblk + blockIdx.x) * 3;
-        o[0] = acc[0];
-        o[1] = acc[1];
-        o[2] = acc[2];
+    __syncthreads();
+    const int nv = (im1 - im0) * 3;
+    if (tid < nv) {
+        const double* r = red[tid / 3][tid % 3];
+        part[((size_t)(im0 + tid / 3) * d.nblk + blockIdx.x) * 3 + tid % 3] = r[0] + r[1] + r[2] + r[3];
     }
 }
 
-// Forces of interior images, velocity update, chain-wide v.F and F.F partials.
-// s3[v] = (|tau|^2, g.tau, l^2) from k_gneb_sum<3>.
+// Forces of the `ipw` interior images from 1 + blockIdx.y * ipw (over the
+// previous forces), partials of v.F and F.F with the velocity that follows
+// (update_v; v.F = 0 otherwise).  s3[v] = (|tau|^2, g.tau, l^2).
 // Image types: 0 normal, 1 climbing (no spring, F = -g + 2 (g.t) t),
 // 2 falling (no spring, F = -g); all per-spin projected.
 template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_force(GnebDims d, T k_spring, T dt_2m, int update_v,
-                                                    const T* __restrict__ x, const T* __restrict__ g,
-                                                    const T* __restrict__ tau, const double* __restrict__ tpart,
-                                                    double* __restrict__ s3, const int* __restrict__ types,
-                                                    T* __restrict__ F, const T* __restrict__ Fp, T* __restrict__ v,
-                                                    double* __restrict__ part,
-    double* __restrict__ fmax_part, const int* __restrict__ stop) {
+__global__ void __launch_bounds__(256) k_gneb_force(GnebDims d, int ipw, T k_spring, T dt_2m, int update_v,
+                                                    const double* __restrict__ scale, const T* __restrict__ x,
+                                                    const T* __restrict__ g, const double* __restrict__ E,
+                                                    const double* __restrict__ tpart, double* __restrict__ s3,
+                                                    const int* __restrict__ types, T* __restrict__ F,
+                                                    double* __restrict__ part, double* __restrict__ fmax_part,
+                                                    const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int im = blockIdx.y + 1;
-    // |tau|^2, g.tau, l^2 of this image and of the one before
-    double s_im[3], s_prev[3];
-    row_sum<3>(tpart, d.nblk, im, s_im);
-    row_sum<3>(tpart, d.nblk, im - 1, s_prev);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) s3[im * 3 + k] = s_im[k];
-        if (im == 1)
-            for (int k = 0; k < 3; ++k) s3[k] = s_prev[k];
-    }
-    double acc[2] = {0.0, 0.0};
-    if (i < d.N) {
-        const size_t off = (size_t)im * 3 * d.N;
-        const double tn2 = s_im[0];
-        const double inv = tn2 > 0.0 ? 1.0 / sqrt(tn2) : 0.0;
-        const int type = types[im];
-        const T cpar = type == 1 ? T(2) : (type == 2 ? T(0) : T(1));
-        const T gt = cpar * (T)(s_im[1] * inv);
-        const T fs = type == 0 ? (T)(k_spring * (sqrt(s_im[2]) - sqrt(s_prev[2]))) : T(0);
-        const V3<T> n = load3(x + off, d.N, i);
-        const V3<T> t = T(inv) * load3(tau + off, d.N, i);
-        const V3<T> gi = load3(g + off, d.N, i);
-        V3<T> fe = gt * t - gi;
-        fe = fe - dot(fe, n) * n;
-        const V3<T> f = fe + fs * t;
-        store3(F + off, d.N, i, f);
-        if (update_v) {
-            const V3<T> vn = load3(v + off, d.N, i) + dt_2m * (load3(Fp + off, d.N, i) + f);
-            store3(v + off, d.N, i, vn);
-            acc[0] = (double)dot(vn, f);
+    __shared__ double s[kGnebImages + 1][3];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = blockIdx.x * 256 + tid;
+    const int im0 = 1 + blockIdx.y * ipw, im1 = min(im0 + ipw, d.M - 1);
+    const size_t L3 = (size_t)3 * d.N;
+    const int ic = min(i, d.N - 1);
+    V3<T> nm = load3(x + (im0 - 1) * L3, d.N, ic), n0 = load3(x + im0 * L3, d.N, ic);
+    const T sc = update_v ? (T)*scale : T(0);
+    // |tau|^2, g.tau, l^2 of images im0 - 1 .. im1 - 1
+    for (int r = im0 - 1 + wave; r < im1; r += 4) {
+        double v[3];
+        wave_row_sum<3>(tpart, d.nblk, r, v);
+        if (lane == 0) {
+            for (int k = 0; k < 3; ++k) {
+                s[r - im0 + 1][k] = v[k];
+                if (blockIdx.x == 0 && (r >= im0 || r == 0)) s3[r * 3 + k] = v[k];
+            }
         }
-        acc[1] = (double)dot(f, f);
     }
-    const double f2 = acc[1];
+    __syncthreads();
+    double acc[2] = {0.0, 0.0};
+    double f2 = 0.0;
+    for (int im = im0; im < im1; ++im) {
+        const V3<T> np = load3(x + (im + 1) * L3, d.N, ic);
+        if (i < d.N) {
+            const double* s_im = s[im - im0 + 1];
+            const double tn2 = s_im[0];
+            const double inv = tn2 > 0.0 ? 1.0 / sqrt(tn2) : 0.0;
+            const int type = types[im];
+            const T cpar = type == 1 ? T(2) : (type == 2 ? T(0) : T(1));
+            const T gt = cpar * (T)(s_im[1] * inv);
+            const T fs = type == 0 ? (T)(k_spring * (sqrt(s_im[2]) - sqrt(s[im - im0][2]))) : T(0);
+            double wp, wm;
+            gneb_weights(E[im - 1], E[im], E[im + 1], wp, wm);
+            const V3<T> t = T(inv) * gneb_tau(nm, n0, np, wp, wm);
+            const size_t off = im * L3;
+            const V3<T> gi = load3(g + off, d.N, i);
+            V3<T> fe = gt * t - gi;
+            fe = fe - dot(fe, n0) * n0;
+            const V3<T> f = fe + fs * t;
+            if (update_v) {
+                const V3<T> fp = load3(F + off, d.N, i);
+                const V3<T> vn = sc * fp + dt_2m * (fp + f);
+                acc[0] += (double)dot(vn, f);
+            }
+            store3(F + off, d.N, i, f);
+            const double ff = (double)dot(f, f);
+            acc[1] += ff;
+            f2 = fmax(f2, ff);
+        }
+        nm = n0;
+        n0 = np;
+    }
     block_sums<2>(acc);
+    const size_t o = (size_t)blockIdx.y * d.nblk + blockIdx.x;
     if (fmax_part) {
         const double m = block_max(f2);
-        if (threadIdx.x == 0) fmax_part[(size_t)(im - 1) * d.nblk + blockIdx.x] = m;
+        if (tid == 0) fmax_part[o] = m;
     }
-    if (threadIdx.x == 0) {
-        double* o = part + ((size_t)(im - 1) * d.nblk + blockIdx.x) * 2;
-        o[0] = acc[0];
-        o[1] = acc[1];
+    if (tid == 0) {
+        part[2 * o] = acc[0];
+        part[2 * o + 1] = acc[1];
     }
 }
 
@@ -368,25 +447,6 @@ __global__ void k_gneb_clear_stop(int* __restrict__ stop, int* __restrict__ stop
     if (threadIdx.x == 0) {
         *stop = 0;
         *stop_iter = -1;
-    }
-}
-
-// Velocity projection: v <- (v.F / F.F) F if v.F > 0, else 0; F_prev <- F.
-template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_project(GnebDims d, const double* __restrict__ vf_ff,
-                                                      T* __restrict__ v, const T* __restrict__ F,
-                                                      T* __restrict__ Fp) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const int im = blockIdx.y + 1;
-    if (i >= d.N) return;
-    const double vf = vf_ff[0], ff = vf_ff[1];
-    const T scale = (vf > 0.0 && ff > 0.0) ? (T)(vf / ff) : T(0);
-    const size_t off = (size_t)im * 3 * d.N;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const size_t q = off + (size_t)c * d.N + i;
-        v[q] = scale * F[q];
-        Fp[q] = F[q];
     }
 }
 
