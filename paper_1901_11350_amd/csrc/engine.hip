@@ -124,7 +124,14 @@ struct sp_engine {
     int persist_cfg = 0;              // index into the persistent-path tile configurations
     std::vector<unsigned char> mc_col;  // Metropolis colour of each (cell class, atom)
     int mc_m[3] = {1, 1, 1};            // periods of the colouring
-    int mc_ncol = 0;
+    int mc_ncol = 0;                    // 0: not planned yet
+    int mc_block = 64;                  // threads of a colour's workgroups
+    std::vector<sp::McClass> mc_cls;    // classes, colour by colour
+    std::vector<int> mc_cls_start;      // first class of each colour
+    std::vector<unsigned> mc_blocks;    // workgroups of each colour
+    void* d_mc = nullptr;               // acceptance counts, cone state and classes on the device
+    double* d_mc_rows = nullptr;        // partial rows of observations not yet reduced
+    size_t mc_rows_cap = 0;
     std::string path_label;
 
     size_t esz() const { return precision == SP_F64 ? 8 : 4; }
@@ -220,6 +227,11 @@ void drop_graphs(sp_engine* e) {
 
 void free_state_buffers(sp_engine* e) {
     drop_graphs(e);
+    // the Monte Carlo plan belongs to the bonds
+    e->mc_ncol = 0;
+    dfree(e->d_mc);
+    dfree(*reinterpret_cast<void**>(&e->d_mc_rows));
+    e->mc_rows_cap = 0;
     dfree(e->d_n); dfree(e->d_n2); dfree(e->d_np); dfree(e->d_A); dfree(e->d_g);
     dfree(e->d_gdd); dfree(e->d_gddp); dfree(e->d_pos); dfree(e->d_ddpart);
     dfree(e->dd_table); dfree(e->d_pairs);
@@ -757,23 +769,18 @@ int go_observe_shape3(sp_engine* e, const void* n) {
     return rows;
 }
 
+// Stage 1 of the observables: rows of partials into e->d_partials; returns
+// their number, or a negative status.
 template <typename T>
-int launch_observe(sp_engine* e, const void* n, double* out, long long step, bool with_flag,
-                   const unsigned long long* step_dev = nullptr, int step_off = 0, double tol = 0.0) {
+int launch_observe_partials(sp_engine* e, const void* n) {
+    int rows = e->partial_rows;
     if (e->shape3 >= 0 && !e->ham.ddi && e->ham.n_gauss == 0) {
-        int rows;
         switch (e->shape3) {
             case sp::SH3_SC1: rows = go_observe_shape3<T, sp::SH3_SC1>(e, n); break;
             case sp::SH3_SC2: rows = go_observe_shape3<T, sp::SH3_SC2>(e, n); break;
             default: rows = go_observe_shape3<T, sp::SH3_SC3>(e, n); break;
         }
-        hipLaunchKernelGGL(sp::k_observe_final, dim3(1), dim3(256), 0, e->stream, e->d_partials, rows, out,
-                           with_flag ? e->d_flag : nullptr, e->d_abort_step, step, step_dev, step_off, tol);
-        HIPCHK(e, hipGetLastError());
-        return SP_OK;
-    }
-    if (e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0) {
-        int rows;
+    } else if (e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0) {
         switch (e->shape) {
             case sp::SH_SQ1: rows = go_observe_shape<T, sp::SH_SQ1>(e, n); break;
             case sp::SH_SQ2: rows = go_observe_shape<T, sp::SH_SQ2>(e, n); break;
@@ -782,24 +789,29 @@ int launch_observe(sp_engine* e, const void* n, double* out, long long step, boo
             case sp::SH_TRI2: rows = go_observe_shape<T, sp::SH_TRI2>(e, n); break;
             default: rows = go_observe_shape<T, sp::SH_TRI3>(e, n); break;
         }
-        hipLaunchKernelGGL(sp::k_observe_final, dim3(1), dim3(256), 0, e->stream, e->d_partials, rows, out,
-                           with_flag ? e->d_flag : nullptr, e->d_abort_step, step, step_dev, step_off, tol);
-        HIPCHK(e, hipGetLastError());
-        return SP_OK;
+    } else {
+        const void* gdd = nullptr;
+        if (e->ham.ddi) {
+            int rc = launch_dipole<T>(e, n, e->d_gdd);
+            if (rc) return rc;
+            gdd = e->d_gdd;
+        }
+        if (e->pair_ok)
+            rows = launch_pair<T, sp::PAIR_OBSERVE>(e, nullptr, 0, n, nullptr, gdd, nullptr);
+        else
+            hipLaunchKernelGGL((sp::k_observe_partial<T>), dim3(e->partial_rows), dim3(256), 0, e->stream,
+                               make_lattice(e), make_coef<T>(e), make_phys<T>(e, nullptr), static_cast<const T*>(n),
+                               static_cast<const T*>(gdd), e->d_partials);
     }
-    const void* gdd = nullptr;
-    if (e->ham.ddi) {
-        int rc = launch_dipole<T>(e, n, e->d_gdd);
-        if (rc) return rc;
-        gdd = e->d_gdd;
-    }
-    int rows = e->partial_rows;
-    if (e->pair_ok)
-        rows = launch_pair<T, sp::PAIR_OBSERVE>(e, nullptr, 0, n, nullptr, gdd, nullptr);
-    else
-        hipLaunchKernelGGL((sp::k_observe_partial<T>), dim3(e->partial_rows), dim3(256), 0, e->stream,
-                           make_lattice(e), make_coef<T>(e), make_phys<T>(e, nullptr), static_cast<const T*>(n),
-                           static_cast<const T*>(gdd), e->d_partials);
+    HIPCHK(e, hipGetLastError());
+    return rows;
+}
+
+template <typename T>
+int launch_observe(sp_engine* e, const void* n, double* out, long long step, bool with_flag,
+                   const unsigned long long* step_dev = nullptr, int step_off = 0, double tol = 0.0) {
+    const int rows = launch_observe_partials<T>(e, n);
+    if (rows < 0) return rows;
     hipLaunchKernelGGL(sp::k_observe_final, dim3(1), dim3(256), 0, e->stream, e->d_partials, rows, out,
                        with_flag ? e->d_flag : nullptr, e->d_abort_step, step, step_dev, step_off, tol);
     HIPCHK(e, hipGetLastError());
@@ -1958,57 +1970,111 @@ int dsatur(const std::vector<std::vector<int>>& adj, std::vector<int>& col) {
 // bonds on the ma x mb x mc x n_basis classes must have no loop, and is
 // coloured by DSATUR; the periods giving the fewest colours win (ties to
 // the smaller period product).
+// The plan depends on the geometry and the bonds only and is kept until
+// either is set again.  The periods are tried by increasing product, and the
+// search ends with the first colouring that reaches a lower bound on the
+// colours: one without bonds, three where three bonds close a triangle, two
+// otherwise.  (Colouring every quotient graph of a 30^3 lattice, up to 216
+// classes each, took longer than forty sweeps.)
 int mc_plan(sp_engine* e) {
     const HostGeo& g = e->geo;
+    if (e->mc_ncol > 0) return SP_OK;
     if (e->ham.ddi) return fail(e, SP_E_UNSUPPORTED, "Monte Carlo sweeps do not support the dipole term");
     std::vector<int> cand[3];
     for (int k = 0; k < 3; ++k)
         for (int m = 1; m <= 6; ++m)
             if (m <= g.n[k] && (!g.per[k] || g.n[k] % m == 0)) cand[k].push_back(m);
-    int best = 1 << 30, best_prod = 1 << 30;
+    struct Periods {
+        int ma, mb, mc;
+    };
+    std::vector<Periods> order;
     for (int ma : cand[0])
         for (int mb : cand[1])
-            for (int mc : cand[2]) {
-                const int cells = ma * mb * mc, nodes = cells * g.nb;
-                std::vector<std::vector<int>> adj(nodes);
-                bool ok = true;
-                for (int ia = 0; ia < ma && ok; ++ia)
-                    for (int ib = 0; ib < mb && ok; ++ib)
-                        for (int ic = 0; ic < mc && ok; ++ic)
-                            for (int beta = 0; beta < g.nb && ok; ++beta) {
-                                const int u = ((ia * mb + ib) * mc + ic) * g.nb + beta;
-                                for (int q = e->bstart[beta]; q < e->bstart[beta + 1]; ++q) {
-                                    const HostBond& b = e->bonds[q];
-                                    const int ja = ((ia + b.d[0]) % ma + ma) % ma;
-                                    const int jb = ((ib + b.d[1]) % mb + mb) % mb;
-                                    const int jc = ((ic + b.d[2]) % mc + mc) % mc;
-                                    const int v = ((ja * mb + jb) * mc + jc) * g.nb + b.bj;
-                                    if (v == u) {
-                                        ok = false;
-                                        break;
-                                    }
-                                    adj[u].push_back(v);
-                                    adj[v].push_back(u);
-                                }
-                            }
-                if (!ok) continue;
-                std::vector<int> col;
-                const int K = dsatur(adj, col);
-                if (K < best || (K == best && cells < best_prod)) {
-                    best = K;
-                    best_prod = cells;
-                    e->mc_m[0] = ma;
-                    e->mc_m[1] = mb;
-                    e->mc_m[2] = mc;
-                    e->mc_col.assign(col.begin(), col.end());
+            for (int mc : cand[2]) order.push_back(Periods{ma, mb, mc});
+    std::stable_sort(order.begin(), order.end(),
+                     [](const Periods& x, const Periods& y) { return x.ma * x.mb * x.mc < y.ma * y.mb * y.mc; });
+    int bound = e->bonds.empty() ? 1 : 2;
+    for (const HostBond& p : e->bonds) {
+        for (int q = e->bstart[p.bj]; q < e->bstart[p.bj + 1] && bound == 2; ++q)
+            for (int r = e->bstart[p.bi]; r < e->bstart[p.bi + 1]; ++r) {
+                const HostBond &b = e->bonds[q], &c = e->bonds[r];
+                if (c.bj == b.bj && c.d[0] == p.d[0] + b.d[0] && c.d[1] == p.d[1] + b.d[1] && c.d[2] == p.d[2] + b.d[2]) {
+                    bound = 3;
+                    break;
                 }
             }
+        if (bound == 3) break;
+    }
+    int best = 1 << 30, best_prod = 1 << 30;
+    for (const Periods& o : order) {
+        const int ma = o.ma, mb = o.mb, mc = o.mc;
+        if (best <= bound) break;
+        const int cells = ma * mb * mc, nodes = cells * g.nb;
+        std::vector<std::vector<int>> adj(nodes);
+        bool ok = true;
+        for (int ia = 0; ia < ma && ok; ++ia)
+            for (int ib = 0; ib < mb && ok; ++ib)
+                for (int ic = 0; ic < mc && ok; ++ic)
+                    for (int beta = 0; beta < g.nb && ok; ++beta) {
+                        const int u = ((ia * mb + ib) * mc + ic) * g.nb + beta;
+                        for (int q = e->bstart[beta]; q < e->bstart[beta + 1]; ++q) {
+                            const HostBond& b = e->bonds[q];
+                            const int ja = ((ia + b.d[0]) % ma + ma) % ma;
+                            const int jb = ((ib + b.d[1]) % mb + mb) % mb;
+                            const int jc = ((ic + b.d[2]) % mc + mc) % mc;
+                            const int v = ((ja * mb + jb) * mc + jc) * g.nb + b.bj;
+                            if (v == u) {
+                                ok = false;
+                                break;
+                            }
+                            adj[u].push_back(v);
+                            adj[v].push_back(u);
+                        }
+                    }
+        if (!ok) continue;
+        std::vector<int> col;
+        const int K = dsatur(adj, col);
+        if (K < best || (K == best && cells < best_prod)) {
+            best = K;
+            best_prod = cells;
+            e->mc_m[0] = ma;
+            e->mc_m[1] = mb;
+            e->mc_m[2] = mc;
+            e->mc_col.assign(col.begin(), col.end());
+        }
+    }
     if (best == (1 << 30))
         return fail(e, SP_E_UNSUPPORTED,
                     "no periodic colouring with periods up to 6 keeps bonded sites apart (lattice too short?)");
+    // the classes of each colour, and the workgroups of its launch
+    e->mc_block = e->N < (1 << 20) ? 64 : 256;
+    e->mc_cls.clear();
+    e->mc_cls_start.assign(1, 0);
+    e->mc_blocks.clear();
+    for (int colour = 0; colour < best; ++colour) {
+        long long block = 0;
+        for (int ia = 0; ia < e->mc_m[0]; ++ia)
+            for (int ib = 0; ib < e->mc_m[1]; ++ib)
+                for (int ic = 0; ic < e->mc_m[2]; ++ic)
+                    for (int beta = 0; beta < g.nb; ++beta) {
+                        if (e->mc_col[((ia * e->mc_m[1] + ib) * e->mc_m[2] + ic) * g.nb + beta] != colour) continue;
+                        sp::McClass c{{ia, ib, ic}, beta, {0, 0, 0}, (int)block};
+                        long long count = 1;
+                        for (int k = 0; k < 3; ++k) {
+                            c.n[k] = (g.n[k] - c.first[k] + e->mc_m[k] - 1) / e->mc_m[k];
+                            count *= c.n[k];
+                        }
+                        e->mc_cls.push_back(c);
+                        block += (count + e->mc_block - 1) / e->mc_block;
+                    }
+        e->mc_cls_start.push_back((int)e->mc_cls.size());
+        e->mc_blocks.push_back((unsigned)block);
+    }
     e->mc_ncol = best;
     return SP_OK;
 }
+
+constexpr int64_t kMcObs = 64;    // observations of a run whose rows wait for their reduction
 
 template <typename T>
 int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t observe_every, sp_observation* obs,
@@ -2019,26 +2085,43 @@ int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t o
         if ((rc = dalloc(e, e->d_obs, (size_t)n_obs * sp::OBS_NVALS * sizeof(double)))) return rc;
         e->obs_cap = n_obs;
     }
-    const unsigned blocks = blocks_for(e->N);
-    unsigned int* acc = nullptr;
-    if ((rc = dalloc(e, acc, blocks * sizeof(unsigned int) + e->mc_col.size()))) return rc;
+    // the workspace (kept with the plan): cone state, acceptance counts, classes
+    const unsigned blocks = *std::max_element(e->mc_blocks.begin(), e->mc_blocks.end());
+    const size_t acc_off = 2 * sizeof(double), cls_off = (acc_off + blocks * sizeof(unsigned int) + 15) / 16 * 16;
+    if (!e->d_mc) {
+        if ((rc = dalloc(e, e->d_mc, cls_off + e->mc_cls.size() * sizeof(sp::McClass)))) return rc;
+        const hipError_t up = hipMemcpy(static_cast<char*>(e->d_mc) + cls_off, e->mc_cls.data(),
+                                        e->mc_cls.size() * sizeof(sp::McClass), hipMemcpyHostToDevice);
+        if (up != hipSuccess) {
+            dfree(e->d_mc);
+            return fail(e, SP_E_HIP, std::string("Monte Carlo classes: ") + hipGetErrorString(up));
+        }
+    }
+    double* state = static_cast<double*>(e->d_mc);   // adaptive cone: (cone, accepted count at the previous sweep)
+    unsigned int* acc = reinterpret_cast<unsigned int*>(static_cast<char*>(e->d_mc) + acc_off);
+    const auto* cls = reinterpret_cast<const sp::McClass*>(static_cast<char*>(e->d_mc) + cls_off);
     HIPCHK(e, hipMemsetAsync(acc, 0, blocks * sizeof(unsigned int), e->stream));
-    // the colour table rides behind the acceptance counts
-    unsigned char* col = reinterpret_cast<unsigned char*>(acc + blocks);
-    HIPCHK(e, hipMemcpyAsync(col, e->mc_col.data(), e->mc_col.size(), hipMemcpyHostToDevice, e->stream));
+    // observations are reduced to rows as they are taken and finished up to
+    // kMcObs at a time
+    const int64_t group = std::min<int64_t>(n_obs, kMcObs);
+    const size_t rows_bytes = (size_t)group * e->partial_rows * sp::OBS_NVALS * sizeof(double);
+    if (rows_bytes > e->mc_rows_cap) {
+        if ((rc = dalloc(e, e->d_mc_rows, rows_bytes))) {
+            e->mc_rows_cap = 0;
+            return rc;
+        }
+        e->mc_rows_cap = rows_bytes;
+    }
     const sp::Lattice L = make_lattice(e);
     // decisions in FP64 for every engine precision: FP64 couplings
     const sp::BondCoef<double> C = make_coef64(e);
     const sp::Phys<double> P = make_phys<double>(e, nullptr);
     sp::McArgs<double> M{};
-    M.col = col;
     for (int q = 0; q < 3; ++q) M.cm[q] = e->mc_m[q];
     M.kT = kKB * p->T_K;
     M.cos_cone = std::cos(p->cone_deg * M_PI / 180.0);
-    double* state = nullptr;   // adaptive cone: (cone, accepted count at the previous sweep)
     const bool adaptive = p->target_acceptance > 0.0;
     if (adaptive) {
-        if ((rc = dalloc(e, state, 2 * sizeof(double)))) { dfree(*reinterpret_cast<void**>(&acc)); return rc; }
         const double init[2] = {p->cone_deg, 0.0};
         HIPCHK(e, hipMemcpyAsync(state, init, sizeof(init), hipMemcpyHostToDevice, e->stream));
         HIPCHK(e, hipStreamSynchronize(e->stream));
@@ -2047,27 +2130,34 @@ int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t o
     M.key.seed_lo = (uint32_t)p->seed;
     M.key.seed_hi = (uint32_t)(p->seed >> 32);
     M.key.replica = p->replica;
-    int64_t k = 0;
+    int64_t k = 0, pending = 0;
+    int rows = 0;
     for (int64_t t = 0; t < n_sweeps; ++t) {
         M.key.step_lo = (uint32_t)e->step;
         M.key.step_hi = (uint32_t)(e->step >> 32);
         for (int colour = 0; colour < e->mc_ncol; ++colour) {
-            M.colour = colour;
-            hipLaunchKernelGGL((sp::k_mc_colour<T>), dim3(blocks), dim3(256), 0, e->stream, L, C, P, M,
-                               static_cast<T*>(e->d_n), acc);
+            M.cls = cls + e->mc_cls_start[colour];
+            M.n_cls = e->mc_cls_start[colour + 1] - e->mc_cls_start[colour];
+            hipLaunchKernelGGL((sp::k_mc_colour<T>), dim3(e->mc_blocks[colour]), dim3((unsigned)e->mc_block), 0,
+                               e->stream, L, C, P, M, static_cast<T*>(e->d_n), acc);
         }
         if (adaptive)
             hipLaunchKernelGGL(sp::k_mc_adapt, dim3(1), dim3(256), 0, e->stream, acc, (int)blocks, (long long)e->N,
                                p->target_acceptance, state);
         ++e->step;
         if (observe_every > 0 && (t + 1) % observe_every == 0) {
-            rc = launch_observe<T>(e, e->d_n, e->d_obs + k * sp::OBS_NVALS, (long long)e->step, false);
-            if (rc) {
-                dfree(*reinterpret_cast<void**>(&acc));
-                dfree(*reinterpret_cast<void**>(&state));
-                return rc;
-            }
+            double* own = e->d_partials;
+            e->d_partials = e->d_mc_rows + (size_t)pending * rows * sp::OBS_NVALS;
+            const int got = launch_observe_partials<T>(e, e->d_n);
+            e->d_partials = own;
+            if (got < 0) return got;
+            rows = got;
             ++k;
+            if (++pending == group || k == n_obs) {
+                hipLaunchKernelGGL(sp::k_observe_finals, dim3((unsigned)pending), dim3(256), 0, e->stream,
+                                   e->d_mc_rows, rows, e->d_obs + (size_t)(k - pending) * sp::OBS_NVALS);
+                pending = 0;
+            }
         }
     }
     hipError_t st = hipGetLastError();
@@ -2080,8 +2170,6 @@ int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t o
     if (st == hipSuccess && adaptive)
         st = hipMemcpyAsync(fin, state, sizeof(fin), hipMemcpyDeviceToHost, e->stream);
     if (st == hipSuccess) st = hipStreamSynchronize(e->stream);
-    dfree(*reinterpret_cast<void**>(&acc));
-    dfree(*reinterpret_cast<void**>(&state));
     if (cone_out) *cone_out = fin[0];
     if (st != hipSuccess) return fail(e, SP_E_HIP, std::string("Monte Carlo run: ") + hipGetErrorString(st));
     if (accepted) {
@@ -2889,7 +2977,8 @@ struct sp_gneb {
     sp_engine* e = nullptr;
     int device = 0;
     int M = 0, N = 0, nblk = 0, nblk_e = 0;
-    int ipw_t = 1, ipw_f = 1;   // images per workgroup of the tangent and force kernels
+    int tile = 16;           // side of the gradient tiles (16 or 32)
+    int ipw = 1;             // images per workgroup of the tangent and force kernels (1, 2 or 4)
     double k = 1.0, dt = 0.1, m = 1.0;
     void *x = nullptr, *x2 = nullptr, *F = nullptr, *g = nullptr;   // chain, the chain's other buffer, force, gradient
     double* part = nullptr;  // force partials (v.F, F.F)
@@ -3427,30 +3516,30 @@ int gneb_groups(int images, int ipw) { return (images + ipw - 1) / ipw; }
 // Partials of v.F and F.F.  Up to 2,048 of them every workgroup of the next
 // position step adds them itself (eight per thread, under its loads); more
 // are added by a launch of their own.
-int gneb_parts(const sp_gneb* G) { return G->nblk * gneb_groups(G->M - 2, G->ipw_f); }
+int gneb_parts(const sp_gneb* G) { return G->nblk * gneb_groups(G->M - 2, G->ipw); }
 bool gneb_sum_apart(const sp_gneb* G) { return gneb_parts(G) > 2048; }
 
 // Gradient and energies; move: the position step of the interior images
 // first (the endpoints keep what the first evaluation gave).
-template <typename T, int S, int NDMI>
+template <typename T, int S, int NDMI, int TS>
 void gneb_grad_tiles(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
     sp_engine* e = G->e;
     const sp::GnebDims d = gneb_dims(G);
     const sp::ShapeCoef<double> C = shape_coef_for<double, S>(e);
     const sp::Site2D<double> Q = make_site2d<double>(e, nullptr);
-    const int tiles_x = (e->geo.n[0] + 15) / 16;
+    const int tiles_x = (e->geo.n[0] + TS - 1) / TS;
     T* x = static_cast<T*>(G->x);
     const bool apart = gneb_sum_apart(G);
     const double* src = apart ? G->vf : G->part;
     const int parts = apart ? 1 : gneb_parts(G);
     if (move) {
-        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, true>), dim3(G->nblk_e, G->M - 2), dim3(256), 0, st, d, C,
+        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, true, TS>), dim3(G->nblk_e, G->M - 2), dim3(256), 0, st, d, C,
                            Q, tiles_x, (T)G->dt, (T)(G->dt * G->dt / (2.0 * G->m)), src, parts, G->scale,
                            static_cast<const T*>(G->F), x, static_cast<T*>(G->x2), static_cast<T*>(G->g), G->epart, 1,
                            stop);
         std::swap(G->x, G->x2);
     } else {
-        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, false>), dim3(G->nblk_e, G->M), dim3(256), 0, st, d, C, Q,
+        hipLaunchKernelGGL((sp::k_gneb_grad_tile<T, S, NDMI, false, TS>), dim3(G->nblk_e, G->M), dim3(256), 0, st, d, C, Q,
                            tiles_x, T(0), T(0), src, 0, G->scale, static_cast<const T*>(G->F), x,
                            static_cast<T*>(G->x2), static_cast<T*>(G->g), G->epart, 0, stop);
     }
@@ -3458,8 +3547,14 @@ void gneb_grad_tiles(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
 
 template <typename T, int S>
 void gneb_grad_shape(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
-    if (G->e->shape_ndmi) gneb_grad_tiles<T, S, sp::ShapeTab<S>::NB0>(G, st, move, stop);
-    else gneb_grad_tiles<T, S, 0>(G, st, move, stop);
+    constexpr int ND = sp::ShapeTab<S>::NB0;
+    if (G->tile == 32) {
+        if (G->e->shape_ndmi) gneb_grad_tiles<T, S, ND, 32>(G, st, move, stop);
+        else gneb_grad_tiles<T, S, 0, 32>(G, st, move, stop);
+    } else {
+        if (G->e->shape_ndmi) gneb_grad_tiles<T, S, ND, 16>(G, st, move, stop);
+        else gneb_grad_tiles<T, S, 0, 16>(G, st, move, stop);
+    }
 }
 
 // One evaluation of the forces, after the position step when `move` (an
@@ -3489,11 +3584,19 @@ int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr
     }
     const T* x = static_cast<const T*>(G->x);
     const T* g = static_cast<const T*>(G->g);
-    hipLaunchKernelGGL((sp::k_gneb_tangent<T>), dim3(G->nblk, gneb_groups(G->M - 1, G->ipw_t)), dim3(256), 0, st, d,
-                       G->ipw_t, x, g, G->epart, G->E, G->tpart, stop);
-    hipLaunchKernelGGL((sp::k_gneb_force<T>), dim3(G->nblk, gneb_groups(G->M - 2, G->ipw_f)), dim3(256), 0, st, d,
-                       G->ipw_f, (T)G->k, (T)(G->dt / (2.0 * G->m)), move ? 1 : 0, G->scale, x, g, G->E, G->tpart,
-                       G->s3, G->types, static_cast<T*>(G->F), G->part, stop ? G->fmax : nullptr, stop);
+    auto launch = [&](auto ipw) {
+        constexpr int IPW = decltype(ipw)::value;
+        hipLaunchKernelGGL((sp::k_gneb_tangent<T, IPW>), dim3(G->nblk, gneb_groups(G->M - 1, IPW)), dim3(256), 0, st, d,
+                           x, g, G->epart, G->E, G->tpart, stop);
+        hipLaunchKernelGGL((sp::k_gneb_force<T, IPW>), dim3(G->nblk, gneb_groups(G->M - 2, IPW)), dim3(256), 0, st, d,
+                           (T)G->k, (T)(G->dt / (2.0 * G->m)), move ? 1 : 0, G->scale, x, g, G->E, G->tpart, G->s3,
+                           G->types, static_cast<T*>(G->F), G->part, stop ? G->fmax : nullptr, stop);
+    };
+    switch (G->ipw) {
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 2: launch(std::integral_constant<int, 2>{}); break;
+        default: launch(std::integral_constant<int, 4>{}); break;
+    }
     if (apart)
         hipLaunchKernelGGL((sp::k_gneb_sum<2>), dim3(1), dim3(256), 0, st, G->part, gneb_parts(G), G->vf, stop);
     hipError_t s = hipGetLastError();
@@ -3595,11 +3698,14 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
     G->m = vp_mass;
     (void)hipSetDevice(e->device);
     const size_t vb = (size_t)G->M * 3 * G->N * e->esz();
-    // gradient tiles of 16 x 16 sites or blocks of 256; as many images per
-    // workgroup in the other two kernels as leave about 512 workgroups
-    G->nblk_e = gneb_tiles(G) ? ((e->geo.n[0] + 15) / 16) * ((e->geo.n[1] + 15) / 16) : G->nblk;
-    G->ipw_t = (int)std::max<long long>(1, std::min<long long>(sp::kGnebImages, (long long)G->nblk * (G->M - 1) / 512));
-    G->ipw_f = (int)std::max<long long>(1, std::min<long long>(sp::kGnebImages, (long long)G->nblk * (G->M - 2) / 512));
+    // gradient tiles of 32 x 32 sites while 256 workgroups are left, else 16 x
+    // 16 (blocks of 256 without tiles); up to four images per workgroup in
+    // the other two kernels while 256 workgroups are left
+    auto tiles = [&](int side) { return ((e->geo.n[0] + side - 1) / side) * ((e->geo.n[1] + side - 1) / side); };
+    if ((long long)tiles(32) * (G->M - 2) >= 256) G->tile = 32;
+    G->nblk_e = gneb_tiles(G) ? tiles(G->tile) : G->nblk;
+    G->ipw = 4;
+    while (G->ipw > 1 && (long long)G->nblk * gneb_groups(G->M - 2, G->ipw) < 256) G->ipw /= 2;
     const size_t parts = (size_t)(G->M - 2) * G->nblk * 2;
     void** bufs[] = {&G->x, &G->x2, &G->F, &G->g};
     for (void** b : bufs)

@@ -74,9 +74,19 @@ __device__ __forceinline__ void wave_row_sum(const double* __restrict__ part, in
 // partials; every thread receives it.
 __device__ __forceinline__ double gneb_scale(const double* __restrict__ part, int count) {
     double acc[2] = {0.0, 0.0};
-    for (int b = threadIdx.x; b < count; b += 256) {
-        acc[0] += part[2 * b];
-        acc[1] += part[2 * b + 1];
+    for (int b0 = threadIdx.x; b0 < count; b0 += 4 * 256) {
+        double v[4][2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int b = b0 + k * 256;
+            v[k][0] = b < count ? part[2 * b] : 0.0;
+            v[k][1] = b < count ? part[2 * b + 1] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            acc[0] += v[k][0];
+            acc[1] += v[k][1];
+        }
     }
     block_sums<2>(acc);
     __shared__ double bc;
@@ -104,8 +114,6 @@ __device__ __forceinline__ V3<T> gneb_tau(V3<T> nm, V3<T> n0, V3<T> np, double w
     const V3<T> t = T(wp) * (np - n0) + T(wm) * (n0 - nm);
     return t - dot(t, n0) * n0;
 }
-
-constexpr int kGnebImages = 8;    // images per workgroup of the tangent and force kernels, at most
 
 // Maximum over the block (thread 0 receives it).
 __device__ __forceinline__ double block_max(double v) {
@@ -180,21 +188,23 @@ __global__ void __launch_bounds__(256) k_gneb_grad(GnebDims d, Lattice L, BondCo
     if (threadIdx.x == 0) part[(size_t)im * d.nblk_e + blockIdx.x] = acc[0];
 }
 
-// The same on 16 x 16 tiles of one-atom 2D images with a compile-time
+// The same on TS x TS tiles of one-atom 2D images with a compile-time
 // stencil (ragged tiles allowed), after the position step when MOVE: the
 // tile and its R halo are stepped on the way into LDS (FP64 cells) and the
-// tile's own spins stored to the other chain buffer.  16 x 16 has the
-// smallest halo of the 256-site shapes (1.27 and 1.56 times the tile for R =
-// 1 and 2; 64 x 4: 1.55 and 2.1).  The terms are those of shape_terms, in
-// FP64 from the spins as stored.
-template <typename T, int S, int NDMI, bool MOVE>
+// tile's own spins stored to the other chain buffer.  Squares have the
+// smallest halo.  Bound by instructions, so large chains take 32 x 32 tiles,
+// four sites per thread: the halo is 1.13 times the tile (16 x 16: 1.27) and
+// the velocity scale and the energy sum are formed a quarter as often; 16 x
+// 16 where those would leave CUs without work.  The terms are those of
+// shape_terms, in FP64 from the spins as stored.
+template <typename T, int S, int NDMI, bool MOVE, int TS>
 __global__ void __launch_bounds__(256)
     k_gneb_grad_tile(GnebDims d, ShapeCoef<double> C, Site2D<double> Q, int tiles_x, T dt, T half_dt2_m,
                      const double* __restrict__ fpart, int parts, double* __restrict__ scale_out,
                      const T* __restrict__ F, const T* __restrict__ x, T* __restrict__ xn, T* __restrict__ g,
                      double* __restrict__ part, int im0, const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    constexpr int TX = 16, TY = 16, NT = 256;
+    constexpr int TX = TS, TY = TS, NT = 256, SITES = TS * TS / NT;
     constexpr int R = ShapeTab<S>::R, W = TX + 2 * R, H = TY + 2 * R, P = W * H, KST = (P + NT - 1) / NT;
     __shared__ V4<double> sN[P];
     const int im = im0 + blockIdx.y, tile = blockIdx.x;
@@ -248,18 +258,22 @@ __global__ void __launch_bounds__(256)
         }
     }
     __syncthreads();
-    const int ty = tid / TX, tx = tid - ty * TX;
-    const int gx = x0 + tx, gy = y0 + ty;
     double acc[1] = {0.0};
-    if (gx < Q.na && gy < Q.nb) {
-        const int c = (ty + R) * W + (tx + R);
-        const V3<double> ni = lds_cell_xyz(sN, c);
-        const FieldTerms<double> f = shape_terms<double, S, NDMI, W>(C, Q, sN, c, ni);
-        const V3<double> gt = f.z + f.k + f.j + f.d;
-        store3(g + off, N, gx + gy * Q.na, V3<T>{(T)gt.x, (T)gt.y, (T)gt.z});
-        acc[0] = ni.x * f.z.x + ni.y * f.z.y + ni.z * f.z.z +
-                 0.5 * (ni.x * (f.k.x + f.j.x + f.d.x) + ni.y * (f.k.y + f.j.y + f.d.y) +
-                        ni.z * (f.k.z + f.j.z + f.d.z));
+#pragma unroll
+    for (int k = 0; k < SITES; ++k) {
+        const int u = tid + k * NT;
+        const int ty = u / TX, tx = u - ty * TX;
+        const int gx = x0 + tx, gy = y0 + ty;
+        if (gx < Q.na && gy < Q.nb) {
+            const int c = (ty + R) * W + (tx + R);
+            const V3<double> ni = lds_cell_xyz(sN, c);
+            const FieldTerms<double> f = shape_terms<double, S, NDMI, W>(C, Q, sN, c, ni);
+            const V3<double> gt = f.z + f.k + f.j + f.d;
+            store3(g + off, N, gx + gy * Q.na, V3<T>{(T)gt.x, (T)gt.y, (T)gt.z});
+            acc[0] += ni.x * f.z.x + ni.y * f.z.y + ni.z * f.z.z +
+                      0.5 * (ni.x * (f.k.x + f.j.x + f.d.x) + ni.y * (f.k.y + f.j.y + f.d.y) +
+                             ni.z * (f.k.z + f.j.z + f.d.z));
+        }
     }
     block_sums<1>(acc);
     if (tid == 0) part[(size_t)im * d.nblk_e + tile] = acc[0];
@@ -287,22 +301,26 @@ __global__ void __launch_bounds__(256) k_gneb_sum(const double* __restrict__ par
 }
 
 // Partials of |tau|^2, g.tau (interior images) and of the squared
-// great-circle angle to the next image, for the `ipw` images from
-// blockIdx.y * ipw (images 0 .. M - 2); E of every image.
-template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, int ipw, const T* __restrict__ x,
-                                                      const T* __restrict__ g, const double* __restrict__ epart,
-                                                      double* __restrict__ E, double* __restrict__ part,
-                                                      const int* __restrict__ stop) {
+// great-circle angle to the next image, for the IPW images from
+// blockIdx.y * IPW (images 0 .. M - 2); E of every image.  All spins and
+// gradients of the thread's site are loaded together.
+template <typename T, int IPW>
+__global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, const T* __restrict__ x, const T* __restrict__ g,
+                                                      const double* __restrict__ epart, double* __restrict__ E,
+                                                      double* __restrict__ part, const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    __shared__ double sE[kGnebImages + 2];
-    __shared__ double red[kGnebImages][3][4];
+    __shared__ double sE[IPW + 2];
+    __shared__ double red[IPW][3][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = blockIdx.x * 256 + tid;
-    const int im0 = blockIdx.y * ipw, im1 = min(im0 + ipw, d.M - 1);
+    const int im0 = blockIdx.y * IPW, im1 = min(im0 + IPW, d.M - 1);
     const size_t L3 = (size_t)3 * d.N;
     const int ic = min(i, d.N - 1);
-    V3<T> nm = load3(x + (size_t)max(im0 - 1, 0) * L3, d.N, ic), n0 = load3(x + im0 * L3, d.N, ic);
+    V3<T> xs[IPW + 2], gs[IPW];      // images im0 - 1 .. im0 + IPW
+#pragma unroll
+    for (int k = 0; k < IPW + 2; ++k) xs[k] = load3(x + min(max(im0 - 1 + k, 0), d.M - 1) * L3, d.N, ic);
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) gs[k] = load3(g + min(im0 + k, d.M - 1) * L3, d.N, ic);
     // energies of images im0 - 1 .. im1
     for (int r = max(im0 - 1, 0) + wave; r <= im1; r += 4) {
         double e;
@@ -313,30 +331,29 @@ __global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, int ipw, const
         }
     }
     __syncthreads();
-    for (int im = im0; im < im1; ++im) {
-        const V3<T> np = load3(x + (im + 1) * L3, d.N, ic);
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) {
+        const int im = im0 + k;
+        if (im >= im1) break;
         double acc[3] = {0.0, 0.0, 0.0};
         if (i < d.N) {
-            const V3<T> c = cross(n0, np);
+            const V3<T> c = cross(xs[k + 1], xs[k + 2]);
             // angle in working precision (its inputs are), squared sum in FP64
-            const double ang = (double)atan2(sqrt(dot(c, c)), dot(n0, np));
+            const double ang = (double)atan2(sqrt(dot(c, c)), dot(xs[k + 1], xs[k + 2]));
             acc[2] = ang * ang;
             if (im > 0) {
                 double wp, wm;
-                gneb_weights(sE[im - im0], sE[im - im0 + 1], sE[im - im0 + 2], wp, wm);
-                const V3<T> t = gneb_tau(nm, n0, np, wp, wm);
-                const V3<T> gi = load3(g + im * L3, d.N, i);
+                gneb_weights(sE[k], sE[k + 1], sE[k + 2], wp, wm);
+                const V3<T> t = gneb_tau(xs[k], xs[k + 1], xs[k + 2], wp, wm);
                 acc[0] = (double)dot(t, t);
-                acc[1] = (double)dot(gi, t);
+                acc[1] = (double)dot(gs[k], t);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double v = wave_sum(acc[k]);
-            if (lane == 0) red[im - im0][k][wave] = v;
+        for (int q = 0; q < 3; ++q) {
+            const double v = wave_sum(acc[q]);
+            if (lane == 0) red[k][q][wave] = v;
         }
-        nm = n0;
-        n0 = np;
     }
     __syncthreads();
     const int nv = (im1 - im0) * 3;
@@ -346,13 +363,13 @@ __global__ void __launch_bounds__(256) k_gneb_tangent(GnebDims d, int ipw, const
     }
 }
 
-// Forces of the `ipw` interior images from 1 + blockIdx.y * ipw (over the
+// Forces of the IPW interior images from 1 + blockIdx.y * IPW (over the
 // previous forces), partials of v.F and F.F with the velocity that follows
 // (update_v; v.F = 0 otherwise).  s3[v] = (|tau|^2, g.tau, l^2).
 // Image types: 0 normal, 1 climbing (no spring, F = -g + 2 (g.t) t),
 // 2 falling (no spring, F = -g); all per-spin projected.
-template <typename T>
-__global__ void __launch_bounds__(256) k_gneb_force(GnebDims d, int ipw, T k_spring, T dt_2m, int update_v,
+template <typename T, int IPW>
+__global__ void __launch_bounds__(256) k_gneb_force(GnebDims d, T k_spring, T dt_2m, int update_v,
                                                     const double* __restrict__ scale, const T* __restrict__ x,
                                                     const T* __restrict__ g, const double* __restrict__ E,
                                                     const double* __restrict__ tpart, double* __restrict__ s3,
@@ -360,58 +377,68 @@ __global__ void __launch_bounds__(256) k_gneb_force(GnebDims d, int ipw, T k_spr
                                                     double* __restrict__ part, double* __restrict__ fmax_part,
                                                     const int* __restrict__ stop) {
     if (stop && *stop) return;   // the chain has converged: the rest of the run is skipped
-    __shared__ double s[kGnebImages + 1][3];
+    // per image: 1 / |tau|, g.t (times 2 or 0 by type), spring force, weights
+    __shared__ double s[IPW + 1][3];
+    __shared__ double inv_s[IPW], wp_s[IPW], wm_s[IPW];
+    __shared__ T gt_s[IPW], fs_s[IPW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = blockIdx.x * 256 + tid;
-    const int im0 = 1 + blockIdx.y * ipw, im1 = min(im0 + ipw, d.M - 1);
+    const int im0 = 1 + blockIdx.y * IPW, im1 = min(im0 + IPW, d.M - 1);
     const size_t L3 = (size_t)3 * d.N;
     const int ic = min(i, d.N - 1);
-    V3<T> nm = load3(x + (im0 - 1) * L3, d.N, ic), n0 = load3(x + im0 * L3, d.N, ic);
+    V3<T> xs[IPW + 2], gs[IPW], fp[IPW];
+#pragma unroll
+    for (int k = 0; k < IPW + 2; ++k) xs[k] = load3(x + min(im0 - 1 + k, d.M - 1) * L3, d.N, ic);
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) {
+        const size_t off = min(im0 + k, d.M - 1) * L3;
+        gs[k] = load3(g + off, d.N, ic);
+        fp[k] = load3(F + off, d.N, ic);
+    }
     const T sc = update_v ? (T)*scale : T(0);
     // |tau|^2, g.tau, l^2 of images im0 - 1 .. im1 - 1
     for (int r = im0 - 1 + wave; r < im1; r += 4) {
         double v[3];
         wave_row_sum<3>(tpart, d.nblk, r, v);
         if (lane == 0) {
-            for (int k = 0; k < 3; ++k) {
-                s[r - im0 + 1][k] = v[k];
-                if (blockIdx.x == 0 && (r >= im0 || r == 0)) s3[r * 3 + k] = v[k];
+            for (int q = 0; q < 3; ++q) {
+                s[r - im0 + 1][q] = v[q];
+                if (blockIdx.x == 0 && (r >= im0 || r == 0)) s3[r * 3 + q] = v[q];
             }
         }
     }
     __syncthreads();
+    if (tid < im1 - im0) {
+        const int im = im0 + tid;
+        const double* s_im = s[tid + 1];
+        const double inv = s_im[0] > 0.0 ? 1.0 / sqrt(s_im[0]) : 0.0;
+        const int type = types[im];
+        const T cpar = type == 1 ? T(2) : (type == 2 ? T(0) : T(1));
+        inv_s[tid] = inv;
+        gt_s[tid] = cpar * (T)(s_im[1] * inv);
+        fs_s[tid] = type == 0 ? (T)(k_spring * (sqrt(s_im[2]) - sqrt(s[tid][2]))) : T(0);
+        gneb_weights(E[im - 1], E[im], E[im + 1], wp_s[tid], wm_s[tid]);
+    }
+    __syncthreads();
     double acc[2] = {0.0, 0.0};
     double f2 = 0.0;
-    for (int im = im0; im < im1; ++im) {
-        const V3<T> np = load3(x + (im + 1) * L3, d.N, ic);
-        if (i < d.N) {
-            const double* s_im = s[im - im0 + 1];
-            const double tn2 = s_im[0];
-            const double inv = tn2 > 0.0 ? 1.0 / sqrt(tn2) : 0.0;
-            const int type = types[im];
-            const T cpar = type == 1 ? T(2) : (type == 2 ? T(0) : T(1));
-            const T gt = cpar * (T)(s_im[1] * inv);
-            const T fs = type == 0 ? (T)(k_spring * (sqrt(s_im[2]) - sqrt(s[im - im0][2]))) : T(0);
-            double wp, wm;
-            gneb_weights(E[im - 1], E[im], E[im + 1], wp, wm);
-            const V3<T> t = T(inv) * gneb_tau(nm, n0, np, wp, wm);
-            const size_t off = im * L3;
-            const V3<T> gi = load3(g + off, d.N, i);
-            V3<T> fe = gt * t - gi;
+#pragma unroll
+    for (int k = 0; k < IPW; ++k) {
+        if (im0 + k < im1 && i < d.N) {
+            const V3<T> n0 = xs[k + 1];
+            const V3<T> t = T(inv_s[k]) * gneb_tau(xs[k], n0, xs[k + 2], wp_s[k], wm_s[k]);
+            V3<T> fe = gt_s[k] * t - gs[k];
             fe = fe - dot(fe, n0) * n0;
-            const V3<T> f = fe + fs * t;
+            const V3<T> f = fe + fs_s[k] * t;
             if (update_v) {
-                const V3<T> fp = load3(F + off, d.N, i);
-                const V3<T> vn = sc * fp + dt_2m * (fp + f);
+                const V3<T> vn = sc * fp[k] + dt_2m * (fp[k] + f);
                 acc[0] += (double)dot(vn, f);
             }
-            store3(F + off, d.N, i, f);
+            store3(F + (im0 + k) * L3, d.N, i, f);
             const double ff = (double)dot(f, f);
             acc[1] += ff;
             f2 = fmax(f2, ff);
         }
-        nm = n0;
-        n0 = np;
     }
     block_sums<2>(acc);
     const size_t o = (size_t)blockIdx.y * d.nblk + blockIdx.x;

@@ -21,16 +21,36 @@ enum {
 
 __device__ __forceinline__ bool is_max_slot(int k) { return k == OBS_TMAX || k == OBS_NDEV; }
 
+// Value of the lane that the DPP control selects (lanes of one row of 16).
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_of(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Butterfly over the 64 lanes (all active): neighbours, pairs, quads and
+// eights through DPP (quad permutes, then mirrors, whose partner holds the
+// same partial as the butterfly's), the four rows of 16 through scalar
+// reads.  The order of the additions is that of six exchanges through LDS,
+// each of which waited on the one before.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    v += dpp<0xB1>(v);      // lane ^ 1
+    v += dpp<0x4E>(v);      // lane ^ 2
+    v += dpp<0x141>(v);     // 7 - lane of each eight
+    v += dpp<0x140>(v);     // 15 - lane of each row
+    return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
 }
 
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmax(v, dpp<0xB1>(v));
+    v = fmax(v, dpp<0x4E>(v));
+    v = fmax(v, dpp<0x141>(v));
+    v = fmax(v, dpp<0x140>(v));
+    return fmax(fmax(lane_of(v, 0), lane_of(v, 16)), fmax(lane_of(v, 32), lane_of(v, 48)));
 }
 
 // Reduce acc[OBS_NVALS] across a workgroup of NW wavefronts; thread 0 gets
@@ -141,6 +161,28 @@ __global__ void __launch_bounds__(256) k_observe_final(const double* __restrict_
                 *abort_step = s;
             }
         }
+    }
+}
+
+// Stage 2 of several observations at once, without run control: workgroup q
+// reduces the rows of observation q (rows * OBS_NVALS values each).
+__global__ void __launch_bounds__(256) k_observe_finals(const double* __restrict__ partials, int rows,
+                                                        double* __restrict__ out) {
+    const double* part = partials + (size_t)blockIdx.x * rows * OBS_NVALS;
+    double acc[OBS_NVALS];
+#pragma unroll
+    for (int k = 0; k < OBS_NVALS; ++k) acc[k] = 0.0;
+    for (int r = threadIdx.x; r < rows; r += blockDim.x) {
+#pragma unroll
+        for (int k = 0; k < OBS_NVALS; ++k) {
+            const double v = part[r * OBS_NVALS + k];
+            acc[k] = is_max_slot(k) ? fmax(acc[k], v) : acc[k] + v;
+        }
+    }
+    block_reduce(acc);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < OBS_NVALS; ++k) out[(size_t)blockIdx.x * OBS_NVALS + k] = acc[k];
     }
 }
 
