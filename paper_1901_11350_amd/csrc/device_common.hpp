@@ -45,9 +45,10 @@ __device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c.x;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c.z;
         U4 o;
-        o.x = (uint32_t)(p1 >> 32) ^ c.y ^ k0;
+        // three-way xor in one instruction (truth table 0x96)
+        o.x = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c.y, k0, 0x96);
         o.y = (uint32_t)p1;
-        o.z = (uint32_t)(p0 >> 32) ^ c.w ^ k1;
+        o.z = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c.w, k1, 0x96);
         o.w = (uint32_t)p0;
         c = o;
         k0 += 0x9E3779B9u;

@@ -676,8 +676,10 @@ int pair_setup(sp_engine* e) {
     const size_t jb = J.size() * sizeof(J[0]), db = D.size() * sizeof(D[0]);
     int rc = dalloc(e, e->d_pairs, std::max<size_t>(jb + db, 64));
     if (rc) return rc;
-    if (jb) HIPCHK(e, hipMemcpy(e->d_pairs, J.data(), jb, hipMemcpyHostToDevice));
-    if (db) HIPCHK(e, hipMemcpy(static_cast<char*>(e->d_pairs) + jb, D.data(), db, hipMemcpyHostToDevice));
+    std::vector<char> both(jb + db);
+    if (jb) std::memcpy(both.data(), J.data(), jb);
+    if (db) std::memcpy(both.data() + jb, D.data(), db);
+    if (jb + db) HIPCHK(e, hipMemcpy(e->d_pairs, both.data(), jb + db, hipMemcpyHostToDevice));
     const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>) + jb + db);
     if (bytes > 158 * 1024) return SP_OK;
     if (bytes > 48 * 1024) {
@@ -1116,6 +1118,19 @@ sp::StepCoef<T> step_coef_for(const sp_engine* e) {
     return C;
 }
 
+// Boundary form of an FP32 2D lattice's tile instances (PER in
+// kernels_fused2d.hpp): 1 periodic along both axes, 2 with power-of-two
+// sides as well, where every wrap is a mask; both need 3N values within
+// 32-bit byte offsets.  Measured, with the three-way xors of the generator:
+// triangular 512^2 at 10 K 6.97 -> 6.67 us per step with its share of the
+// observation (648 VALU instructions per tile pass against 844 of form 1),
+// 24 square replicas of 128^2 and 256^2 13.9 -> 11.5 us per step (form 0
+// before).
+int boundary_form(int na, int nb, int per_a, int per_b) {
+    if (!per_a || !per_b || 3LL * na * nb * (long long)sizeof(float) >= (1ll << 32)) return 0;
+    return (na & (na - 1)) == 0 && (nb & (nb - 1)) == 0 ? 2 : 1;
+}
+
 template <typename T, int S, int NDMI, int TX, int TY, int NT, int SOLVER>
 void go_shape(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout) {
     sp::TileMap M{};
@@ -1123,18 +1138,19 @@ void go_shape(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* n
     M.tiles_y = (e->geo.n[1] + TY - 1) / TY;
     const int ntiles = M.tiles_x * M.tiles_y;
     M.xcd_bands = (ntiles >= 8 && ntiles % 8 == 0) ? 1 : 0;
-    // FP32 Depondt on the 64 x 16 x 1024 tiles: a lattice periodic along both
-    // axes (whose spins fit 32-bit byte offsets) takes the instance without
-    // boundary tests
-    if constexpr (sizeof(T) == 4 && SOLVER == sp::SOLVER_DEPONDT && TX == 64 && TY == 16 && NT == 1024) {
-        const long long n_sites = (long long)e->geo.n[0] * e->geo.n[1];
-        if (e->geo.per[0] && e->geo.per[1] && 3 * n_sites * (long long)sizeof(T) < (1ll << 32)) {
-            hipLaunchKernelGGL((sp::k_fused2d_shape<T, S, NDMI, TX, TY, NT, SOLVER, true>), dim3((unsigned)ntiles),
-                               dim3(NT), 0, e->stream, step_coef_for<T, S>(e), make_site2d<T>(e, p),
-                               make_step_llg<T>(e, p, step), M, e->d_flag, static_cast<const T*>(nin),
-                               static_cast<T*>(nout));
-            return;
-        }
+    // FP32 Depondt on the 64 x 16 x 1024 and 32 x 16 x 512 tiles: periodic
+    // lattices take the instances of their boundary form
+    if constexpr (sizeof(T) == 4 && SOLVER == sp::SOLVER_DEPONDT &&
+                  ((TX == 64 && TY == 16 && NT == 1024) || (TX == 32 && TY == 16 && NT == 512))) {
+        auto go = [&](auto per) {
+            hipLaunchKernelGGL((sp::k_fused2d_shape<T, S, NDMI, TX, TY, NT, SOLVER, decltype(per)::value>),
+                               dim3((unsigned)ntiles), dim3(NT), 0, e->stream, step_coef_for<T, S>(e),
+                               make_site2d<T>(e, p), make_step_llg<T>(e, p, step), M, e->d_flag,
+                               static_cast<const T*>(nin), static_cast<T*>(nout));
+        };
+        const int form = boundary_form(e->geo.n[0], e->geo.n[1], e->geo.per[0], e->geo.per[1]);
+        if (form == 2) return go(std::integral_constant<int, 2>{});
+        if (form == 1) return go(std::integral_constant<int, 1>{});
     }
     hipLaunchKernelGGL((sp::k_fused2d_shape<T, S, NDMI, TX, TY, NT, SOLVER>), dim3((unsigned)ntiles), dim3(NT), 0, e->stream,
                        step_coef_for<T, S>(e), make_site2d<T>(e, p), make_step_llg<T>(e, p, step), M, e->d_flag,
@@ -2435,7 +2451,7 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
             return rc;
         }
     }
-    if ((rc = DISPATCH(e, upload_ham, e)) || (rc = DISPATCH(e, pair_setup, e)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
+    if ((rc = DISPATCH(e, upload_ham, e)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
         free_state_buffers(e);
         e->has_ham = false;
         e->has_spins = false;
@@ -2475,6 +2491,15 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
                 if (b.shell == 0 && (b.D[0] != 0.0 || b.D[1] != 0.0)) e->shape_ndmi = 1;
             e->path = "shape2d";
         }
+    }
+    // lattices with a 2D stencil have kernels of their own for everything the
+    // pair tiles do
+    e->pair_ok = false;
+    if (e->shape < 0 && (rc = DISPATCH(e, pair_setup, e))) {
+        free_state_buffers(e);
+        e->has_ham = false;
+        e->has_spins = false;
+        return rc;
     }
     // 3D one-atom lattices: streamed fused path when the bond table matches a
     // compile-time simple-cubic stencil (DMI on the first shell only)
@@ -3013,7 +3038,8 @@ struct sp_batch {
     float* arena = nullptr;
     size_t arena_floats = 0;
     sp::ReplicaDesc<float>* d_reps = nullptr;
-    int2* d_work = nullptr;
+    sp::BatchWork<float>* d_work = nullptr;   // tiles of the tiled replicas
+    int form_start[4] = {0, 0, 0, 0};         // first tile of each boundary form (kernels_fused2d.hpp)
     int n_work = 0;
     int* d_res32 = nullptr;
     int* d_res64 = nullptr;
@@ -3065,7 +3091,7 @@ void batch_drop_graphs(sp_batch* b) {
 int batch_build_work(sp_batch* b) {
     const TileCfg& tc = kBatchCfgs[b->cfg];
     std::vector<sp::ReplicaDesc<float>> desc(b->reps.size());
-    std::vector<int2> work;
+    std::vector<sp::BatchWork<float>> work, by_form[3];
     std::vector<int> r32, r64;
     for (size_t r = 0; r < b->reps.size(); ++r) {
         const BatchRep& R = b->reps[r];
@@ -3092,9 +3118,17 @@ int batch_build_work(sp_batch* b) {
             r64.push_back((int)r);
         } else {
             const int tiles_y = (R.nb + tc.TY - 1) / tc.TY;
-            for (int t = 0; t < D.tiles_x * tiles_y; ++t) work.push_back(make_int2((int)r, t));
+            // a replica takes the boundary form it has as an engine of its own
+            auto& to = by_form[boundary_form(R.na, R.nb, R.per_a, R.per_b)];
+            for (int t = 0; t < D.tiles_x * tiles_y; ++t)
+                to.push_back(sp::BatchWork<float>{D, (t % D.tiles_x) * tc.TX, (t / D.tiles_x) * tc.TY});
         }
     }
+    for (int f = 0; f < 3; ++f) {
+        b->form_start[f] = (int)work.size();
+        work.insert(work.end(), by_form[f].begin(), by_form[f].end());
+    }
+    b->form_start[3] = (int)work.size();
     void* p = b->d_reps; dfree(p); b->d_reps = nullptr;
     p = b->d_work; dfree(p); b->d_work = nullptr;
     p = b->d_res32; dfree(p); b->d_res32 = nullptr;
@@ -3110,7 +3144,7 @@ int batch_build_work(sp_batch* b) {
     };
     int rc;
     if ((rc = up(b->d_reps, desc.data(), desc.size() * sizeof(desc[0])))) return rc;
-    if ((rc = up(b->d_work, work.data(), work.size() * sizeof(int2)))) return rc;
+    if ((rc = up(b->d_work, work.data(), work.size() * sizeof(work[0])))) return rc;
     if ((rc = up(b->d_res32, r32.data(), r32.size() * sizeof(int)))) return rc;
     if ((rc = up(b->d_res64, r64.data(), r64.size() * sizeof(int)))) return rc;
     b->n_work = (int)work.size();
@@ -3156,15 +3190,24 @@ void batch_launch_resident(sp_batch* b, hipStream_t s, int n_steps) {
                            b->C, b->Q, b->d_reps, b->d_res64, b->d_step, n_steps);
 }
 
+template <int S, int NDMI, int PER>
+void batch_launch_form(sp_batch* b, hipStream_t s, int k, int parity) {
+    const int n = b->form_start[PER + 1] - b->form_start[PER];
+    if (n == 0) return;
+    const auto* work = b->d_work + b->form_start[PER];
+    if (b->cfg == 1)
+        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 64, 16, 1024, PER>), dim3(n), dim3(1024), 0, s, b->SC,
+                           b->Q, work, b->d_step, k, parity);
+    else
+        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 32, 16, 512, PER>), dim3(n), dim3(512), 0, s, b->SC, b->Q,
+                           work, b->d_step, k, parity);
+}
+
 template <int S, int NDMI>
 void batch_launch_tiled(sp_batch* b, hipStream_t s, int k, int parity) {
-    if (!b->n_work) return;
-    if (b->cfg == 1)
-        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 64, 16, 1024>), dim3(b->n_work), dim3(1024), 0, s, b->SC,
-                           b->Q, b->d_reps, b->d_work, b->d_step, k, parity);
-    else
-        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 32, 16, 512>), dim3(b->n_work), dim3(512), 0, s, b->SC,
-                           b->Q, b->d_reps, b->d_work, b->d_step, k, parity);
+    batch_launch_form<S, NDMI, 0>(b, s, k, parity);
+    batch_launch_form<S, NDMI, 1>(b, s, k, parity);
+    batch_launch_form<S, NDMI, 2>(b, s, k, parity);
 }
 
 template <int S>

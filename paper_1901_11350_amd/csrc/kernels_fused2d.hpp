@@ -394,21 +394,37 @@ struct TileLDS {
     V4<T> sP[PP];
 };
 
+// Boundary form of a tile instance (PER): 0 any boundary; 1 both axes
+// periodic; 2 both axes periodic with power-of-two sides, where the wrap is
+// one mask (in the general form every wave with a cell past an edge runs a
+// remainder of some 25 instructions, three to five times per step).
+template <int PER>
+__device__ __forceinline__ int wrap_cell(int g, int n, int per, bool& in) {
+    if constexpr (PER == 2) return g & (n - 1);
+    else return wrap_once(g, n, PER ? 1 : per, in);
+}
+// Site of cell (gx, gy) of a lattice na wide.
+template <int PER>
+__device__ __forceinline__ int cell_index(int gx, int gy, int na) {
+    if constexpr (PER == 2) return gx + (gy << (31 - __builtin_clz(na)));
+    else return gx + gy * na;
+}
+
 // Global site of the predictor-frame cell (px, py), or in = false for a
 // cell outside an open lattice (PER: both axes periodic, never).
-template <typename T, int S, int TX, int TY, bool PER = false>
+template <typename T, int S, int TX, int TY, int PER = 0>
 __device__ __forceinline__ int cell_site(const Site2D<T>& Q, int x0, int y0, int px, int py, bool& in) {
     constexpr int R = ShapeTab<S>::R;
     in = true;
-    const int gx = wrap_once(x0 - R + px, Q.na, PER ? 1 : Q.per_a, in);
-    const int gy = wrap_once(y0 - R + py, Q.nb, PER ? 1 : Q.per_b, in);
-    return gx + gy * Q.na;
+    const int gx = wrap_cell<PER>(x0 - R + px, Q.na, Q.per_a, in);
+    const int gy = wrap_cell<PER>(y0 - R + py, Q.nb, Q.per_b, in);
+    return cell_index<PER>(gx, gy, Q.na);
 }
 
 // External plus thermal field of a predictor-frame cell (the base of
 // shape_B_aos): depends only on the site, the step and the seed, so it is
 // formed while the spins are still in flight.
-template <typename T, int S, int TX, int TY, bool PER = false>
+template <typename T, int S, int TX, int TY, int PER = 0>
 __device__ __forceinline__ V3<T> cell_base(const StepCoef<T>& C, const Site2D<T>& Q, const LLGArgs<T>& A, int x0,
                                            int y0, int px, int py) {
     bool in;
@@ -443,7 +459,7 @@ __device__ __forceinline__ void ring_cell(int h, int& px, int& py) {
 //   SIB:     x solves the midpoint stage with A frozen; sP holds the
 //            midpoint m = (n + x)/2 (Appendix C), returns nothing.
 // Cells that fall outside an open lattice hold a zero spin.
-template <typename T, int S, int NDMI, int TX, int TY, int SOLVER, bool PER = false>
+template <typename T, int S, int NDMI, int TX, int TY, int SOLVER, int PER = 0>
 __device__ __forceinline__ V3<T> predict_cell(const StepCoef<T>& C, const Site2D<T>& Q, const LLGArgs<T>& A, int x0,
                                               int y0, int px, int py, TileLDS<T, S, TX, TY>& L, V3<T> base) {
     using TL = TileLDS<T, S, TX, TY>;
@@ -504,7 +520,7 @@ __device__ __forceinline__ V3<T> correct_cell(const StepCoef<T>& C, const Site2D
 // t owns tile sites t + j NT: it computes their predictor, keeps A and the
 // thermal field in registers, and computes their corrector; the ring of
 // predictor cells around the tile is shared out over the threads between.
-template <typename T, int S, int NDMI, int TX, int TY, int NT, int SOLVER = SOLVER_DEPONDT, bool PER = false>
+template <typename T, int S, int NDMI, int TX, int TY, int NT, int SOLVER = SOLVER_DEPONDT, int PER = 0>
 __device__ __forceinline__ void fused2d_tile(const StepCoef<T>& C, const Site2D<T>& Q, const LLGArgs<T>& A,
                                              int x0, int y0, const T* __restrict__ n, T* __restrict__ nout,
                                              TileLDS<T, S, TX, TY>& L) {
@@ -524,15 +540,15 @@ __device__ __forceinline__ void fused2d_tile(const StepCoef<T>& C, const Site2D<
     for (int k = 0; k < KST; ++k) {
         const int idx = tid + k * NT;
         // (cells past the staged frame are never stored)
-        if constexpr (!PER) st[k] = V3<T>{T(0), T(0), T(0)};
+        if constexpr (PER == 0) st[k] = V3<T>{T(0), T(0), T(0)};
         if (idx < PN) {
             const int ly = idx / WN, lx = idx - ly * WN;
             bool in = true;
-            const int gx = wrap_once(x0 - 2 * R + lx, Q.na, PER ? 1 : Q.per_a, in);
-            const int gy = wrap_once(y0 - 2 * R + ly, Q.nb, PER ? 1 : Q.per_b, in);
+            const int gx = wrap_cell<PER>(x0 - 2 * R + lx, Q.na, Q.per_a, in);
+            const int gy = wrap_cell<PER>(y0 - 2 * R + ly, Q.nb, Q.per_b, in);
             if (in) {
-                const int g = gx + gy * Q.na;
-                if constexpr (PER) {
+                const int g = cell_index<PER>(gx, gy, Q.na);
+                if constexpr (PER != 0) {
                     // 32-bit byte offsets (the host takes this instance only
                     // when 3N values have them)
                     const uint32_t b = (uint32_t)g * (uint32_t)sizeof(T);
@@ -595,8 +611,8 @@ __device__ __forceinline__ void fused2d_tile(const StepCoef<T>& C, const Site2D<
         const int gx = x0 + tx, gy = y0 + ty;
         if (gx >= Q.na || gy >= Q.nb) continue;
         const V3<T> o = correct_cell<T, S, NDMI, TX, TY, SOLVER>(C, Q, A, tx, ty, L, keepA[j], keepB[j]);
-        const int gi = gx + gy * Q.na;
-        if constexpr (PER) {
+        const int gi = cell_index<PER>(gx, gy, Q.na);
+        if constexpr (PER != 0) {
             const uint32_t b = (uint32_t)gi * (uint32_t)sizeof(T);
             store_out(ptr_byte(nout, b), o.x);
             store_out(ptr_byte(nout + N, b), o.y);
@@ -609,10 +625,10 @@ __device__ __forceinline__ void fused2d_tile(const StepCoef<T>& C, const Site2D<
     }
 }
 
-// PER: both axes periodic, so the boundary tests and zero fills of cells
+// PER != 0: both axes periodic, so the boundary tests and zero fills of cells
 // outside the lattice are compiled out, and spins are addressed by 32-bit
 // byte offsets (the host takes it only when 3N values have them).
-template <typename T, int S, int NDMI, int TX, int TY, int NT, int SOLVER = SOLVER_DEPONDT, bool PER = false>
+template <typename T, int S, int NDMI, int TX, int TY, int NT, int SOLVER = SOLVER_DEPONDT, int PER = 0>
 __global__ void __launch_bounds__(NT) k_fused2d_shape(StepCoef<T> C, Site2D<T> Q, LLGArgs<T> A_arg, TileMap M,
                                                       const int* __restrict__ abort_flag, const T* __restrict__ n,
                                                       T* __restrict__ nout) {
@@ -659,25 +675,29 @@ __device__ __forceinline__ void replica_args(const ReplicaDesc<T>& R, unsigned l
     A.key.replica = R.replica;
 }
 
+// A tile of a tiled replica, with the replica's own description (one load
+// between the kernel arguments and the spins).
+template <typename T>
+struct BatchWork {
+    ReplicaDesc<T> r;
+    int x0, y0;
+};
+
 // One Depondt step of every tile of every tiled replica: work item
 // (replica, tile) per workgroup.  The step number is *step_base + k, so a
 // captured graph of k = 0..K-1 can be replayed after step_base advances.
-template <typename T, int S, int NDMI, int TX, int TY, int NT>
-__global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, const ReplicaDesc<T>* __restrict__ reps,
-                                                    const int2* __restrict__ work,
+template <typename T, int S, int NDMI, int TX, int TY, int NT, int PER>
+__global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, const BatchWork<T>* __restrict__ work,
                                                     const unsigned long long* __restrict__ step_base, int k,
                                                     int parity) {
     __shared__ TileLDS<T, S, TX, TY> L;
-    const int2 wk = work[blockIdx.x];
-    const ReplicaDesc<T> R = reps[wk.x];
+    const BatchWork<T> W = work[blockIdx.x];
     LLGArgs<T> A;
-    replica_args(R, *step_base + (unsigned long long)k, Q, A);
-    const int ty0 = wk.y / R.tiles_x;
+    replica_args(W.r, *step_base + (unsigned long long)k, Q, A);
     const bool odd = (parity ^ (k & 1)) != 0;
-    T* const b0 = R.n[0];
-    T* const b1 = R.n[1];
-    fused2d_tile<T, S, NDMI, TX, TY, NT>(C, Q, A, (wk.y - ty0 * R.tiles_x) * TX, ty0 * TY, odd ? b1 : b0,
-                                         odd ? b0 : b1, L);
+    T* const b0 = W.r.n[0];
+    T* const b1 = W.r.n[1];
+    fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, PER>(C, Q, A, W.x0, W.y0, odd ? b1 : b0, odd ? b0 : b1, L);
 }
 
 // Resident replicas: one workgroup holds a whole LX x LY replica (plus an R
