@@ -29,6 +29,7 @@
 #include "kernels_mc.hpp"
 #include "kernels_fused3d.hpp"
 #include "kernels_persist2d.hpp"
+#include "kernels_resident.hpp"
 #include "kernels_stencil.hpp"
 #include "kernels_pairs.hpp"
 
@@ -121,6 +122,7 @@ struct sp_engine {
     int shape3_ndmi = 0;              // DMI on the first shell
     int shape3_dk = 0;                // sp::Dmi3 of the streamed step kernel
     int tile3_cfg = 0;                // index into the 3D tile configurations
+    bool path_chosen = false;         // the step path was set by name (no resident launches)
     int persist_cfg = 0;              // index into the persistent-path tile configurations
     std::vector<unsigned char> mc_col;  // Metropolis colour of each (cell class, atom)
     int mc_m[3] = {1, 1, 1};            // periods of the colouring
@@ -1494,8 +1496,69 @@ void launch_shape3(sp_engine* e, const sp_llg_params* p, uint64_t step, const vo
         go_cfg3<T, sp::SOLVER_DEPONDT>(e, p, step, nin, nout);
 }
 
+// ------------------------------------------------- resident path (small 2D)
+// Lattices of at most 1024 sites (FP32: 2048) with a compile-time stencil, on
+// the step path the engine chose itself, run in one workgroup
+// (kernels_resident.hpp): beyond, the tile kernels spread the sites over more
+// CUs for less than the launch costs.
+bool resident_fits(const sp_engine* e) {
+    return e->shape >= 0 && e->N <= (e->precision == SP_F64 ? sp::resident_sites<double>() : sp::resident_sites<float>());
+}
+bool resident_ok(const sp_engine* e) {
+    return resident_fits(e) && !e->path_chosen && std::strcmp(e->path, "shape2d") == 0;
+}
+
+constexpr int kResidentMaxChunk = 1 << 14;   // steps per launch
+
+template <typename T, int S, int SOLVER>
+void go_resident(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout, int n_steps) {
+    auto go = [&](auto ndmi, auto pt) {
+        constexpr int PT = decltype(pt)::value;
+        const dim3 block((unsigned)((e->N + 64 * PT - 1) / (64 * PT) * 64));
+        hipLaunchKernelGGL((sp::k_resident2d<T, S, decltype(ndmi)::value, SOLVER, PT>), dim3(1), block, 0, e->stream,
+                           step_coef_for<T, S>(e), make_site2d<T>(e, p), make_llg<T>(p, step, p->replica), e->d_flag,
+                           static_cast<const T*>(nin), static_cast<T*>(nout), n_steps);
+    };
+    constexpr std::integral_constant<int, sp::ShapeTab<S>::NB0> dmi{};
+    constexpr std::integral_constant<int, 0> none{};
+    constexpr std::integral_constant<int, 1> one{};
+    if constexpr (sizeof(T) == 4) {
+        if (e->N > 1024) {
+            constexpr std::integral_constant<int, 2> two{};
+            if (e->shape_ndmi) go(dmi, two);
+            else go(none, two);
+            return;
+        }
+    }
+    if (e->shape_ndmi) go(dmi, one);
+    else go(none, one);
+}
+
+template <typename T, int SOLVER>
+void resident_shape(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout, int n_steps) {
+    switch (e->shape) {
+        case sp::SH_SQ1: go_resident<T, sp::SH_SQ1, SOLVER>(e, p, step, nin, nout, n_steps); break;
+        case sp::SH_SQ2: go_resident<T, sp::SH_SQ2, SOLVER>(e, p, step, nin, nout, n_steps); break;
+        case sp::SH_SQ3: go_resident<T, sp::SH_SQ3, SOLVER>(e, p, step, nin, nout, n_steps); break;
+        case sp::SH_TRI1: go_resident<T, sp::SH_TRI1, SOLVER>(e, p, step, nin, nout, n_steps); break;
+        case sp::SH_TRI2: go_resident<T, sp::SH_TRI2, SOLVER>(e, p, step, nin, nout, n_steps); break;
+        default: go_resident<T, sp::SH_TRI3, SOLVER>(e, p, step, nin, nout, n_steps); break;
+    }
+}
+
+// n_steps steps from nin to nout (which may be the same buffer).
+template <typename T>
+int launch_resident(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout, int n_steps) {
+    if (p->solver == SP_SOLVER_HEUN) resident_shape<T, sp::SOLVER_HEUN>(e, p, step, nin, nout, n_steps);
+    else if (p->solver == SP_SOLVER_SIB) resident_shape<T, sp::SOLVER_SIB>(e, p, step, nin, nout, n_steps);
+    else resident_shape<T, sp::SOLVER_DEPONDT>(e, p, step, nin, nout, n_steps);
+    HIPCHK(e, hipGetLastError());
+    return SP_OK;
+}
+
 template <typename T>
 int launch_step(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout) {
+    if (resident_ok(e)) return launch_resident<T>(e, p, step, nin, nout, 1);
     if (std::strcmp(e->path, "shape2d") == 0 || std::strcmp(e->path, "persist2d") == 0) {
         launch_shape<T>(e, p, step, nin, nout);
         HIPCHK(e, hipGetLastError());
@@ -1883,9 +1946,24 @@ int run_impl(sp_engine* e, const sp_llg_params* p, int64_t n_steps, int64_t obse
             }
         }
     }
+    // small 2D lattices: one launch per observation interval, in place
+    const bool resident = resident_ok(e);
+    for (int64_t r = 0; resident && r < n_steps;) {
+        int64_t chunk = observe_every > 0 ? observe_every - r % observe_every : n_steps - r;
+        chunk = std::min<int64_t>(std::min<int64_t>(chunk, n_steps - r), kResidentMaxChunk);
+        if ((rc = launch_resident<T>(e, p, e->step, e->d_n, e->d_n, (int)chunk))) return rc;
+        e->step += (uint64_t)chunk;
+        r += chunk;
+        if (observe_every > 0 && r % observe_every == 0) {
+            rc = launch_observe<T>(e, e->d_n, e->d_obs + k * sp::OBS_NVALS, (long long)e->step, true, nullptr, 0, tol);
+            if (rc) return rc;
+            ++k;
+        }
+    }
+    const bool whole = persist || resident;   // the run is enqueued
     int64_t t = 0;
     const int64_t C = observe_every > 0 ? observe_every : kGraphChunk;
-    if (!persist && e->graphs_on && !e->ham.ddi && C <= kGraphMaxChunk && n_steps >= C) {
+    if (!whole && e->graphs_on && !e->ham.ddi && C <= kGraphMaxChunk && n_steps >= C) {
         for (const int64_t chunks = n_steps / C; t < chunks * C; t += C) {
             hipGraphExec_t x = nullptr;
             if ((rc = chunk_graph<T>(e, p, (int)C, observe_every > 0, tol, &x))) return rc;
@@ -1896,7 +1974,7 @@ int run_impl(sp_engine* e, const sp_llg_params* p, int64_t n_steps, int64_t obse
         }
     }
     fft_chain(e, true);
-    for (; !persist && t < n_steps; ++t) {
+    for (; !whole && t < n_steps; ++t) {
         rc = launch_step<T>(e, p, e->step, e->d_n, e->d_n2);
         if (rc) {
             fft_chain(e, false);
@@ -1937,7 +2015,7 @@ int run_impl(sp_engine* e, const sp_llg_params* p, int64_t n_steps, int64_t obse
         // the steps after the converged observation were skipped: the state
         // is the one observed, and the buffers swapped once per skipped step
         done = (int64_t)(astep - (long long)step0);
-        if ((n_steps - done) % 2) std::swap(e->d_n, e->d_n2);
+        if (!resident && (n_steps - done) % 2) std::swap(e->d_n, e->d_n2);
         e->step = step0 + (uint64_t)done;
     }
     if (steps_done) *steps_done = done;
@@ -2465,6 +2543,7 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
     e->has_ham = true;
 
     // step path
+    e->path_chosen = false;
     const HostGeo& g = e->geo;
     bool fused = g.nb == 1 && g.n[2] == 1 && e->planar && !H.ddi && H.n_gauss == 0 && e->R <= 2 &&
                  (int)bonds.size() <= sp::kMaxStencil;
@@ -2880,6 +2959,7 @@ int sp_set_step_path(sp_engine* e, const char* name) {
     } else {
         return fail(e, SP_E_ARG, "unknown step path " + s);
     }
+    e->path_chosen = true;
     e->path_label = e->path;
     if (std::strcmp(e->path, "shape2d") == 0) e->path_label += std::string("/") + kTileCfgs[e->tile_cfg].name;
     if (std::strcmp(e->path, "shape3d") == 0) e->path_label += std::string("/") + kTile3Cfgs[e->tile3_cfg].name;
@@ -2922,6 +3002,12 @@ int sp_autotune(sp_engine* e, const sp_llg_params* p, int n_steps, double* ms_pe
         }
     }
     const std::string keep_label = e->path_label;
+    const bool keep_chosen = e->path_chosen;
+    // the resident launches of a small lattice, on the default tile's name
+    const std::string resident = std::string("shape2d/") + kTileCfgs[e->precision == SP_F64 ? 0 : 4].name;
+    const size_t resident_at = cands.size();
+    if (resident_fits(e)) cands.push_back(resident);
+    size_t best_at = cands.size();
     const uint64_t keep_step = e->step;
     const size_t bytes = 3 * (size_t)e->N * e->esz();
     void* backup = nullptr;
@@ -2936,6 +3022,7 @@ int sp_autotune(sp_engine* e, const sp_llg_params* p, int n_steps, double* ms_pe
     }
     for (size_t c = 0; out == SP_OK && c < cands.size(); ++c) {
         if ((rc = sp_set_step_path(e, cands[c].c_str()))) { out = rc; break; }
+        e->path_chosen = c != resident_at;
         float ms = 0.0f;
         const bool pers = std::strcmp(e->path, "persist2d") == 0 && p->solver == SP_SOLVER_DEPONDT;
         if (pers) {
@@ -2945,6 +3032,12 @@ int sp_autotune(sp_engine* e, const sp_llg_params* p, int n_steps, double* ms_pe
             if (!rc) rc = DISPATCH(e, launch_persist, e, p, 1, false);
             if (!rc && hipEventRecord(t0, e->stream) != hipSuccess) rc = SP_E_HIP;
             if (!rc) rc = DISPATCH(e, launch_persist, e, p, n_steps, false);
+        } else if (c == resident_at) {
+            rc = DISPATCH(e, launch_resident, e, p, e->step, e->d_n, e->d_n, 1);
+            if (!rc && hipEventRecord(t0, e->stream) != hipSuccess) rc = SP_E_HIP;
+            for (int k = 0; !rc && k < n_steps; k += kResidentMaxChunk)
+                rc = DISPATCH(e, launch_resident, e, p, keep_step + k, e->d_n, e->d_n,
+                              std::min(n_steps - k, kResidentMaxChunk));
         } else {
             // warm-up (code load, caches), then the timed steps
             rc = DISPATCH(e, launch_step, e, p, e->step, e->d_n, e->d_n2);
@@ -2968,6 +3061,7 @@ int sp_autotune(sp_engine* e, const sp_llg_params* p, int n_steps, double* ms_pe
         if (ms / n_steps < best) {
             best = ms / n_steps;
             best_name = cands[c];
+            best_at = c;
         }
     }
     if (t0) (void)hipEventDestroy(t0);
@@ -2976,6 +3070,7 @@ int sp_autotune(sp_engine* e, const sp_llg_params* p, int n_steps, double* ms_pe
     dfree(backup);
     e->step = keep_step;
     const int rc2 = sp_set_step_path(e, out == SP_OK ? best_name.c_str() : keep_label.c_str());
+    e->path_chosen = out == SP_OK ? best_at != resident_at : keep_chosen;
     if (out == SP_OK && ms_per_step) *ms_per_step = best;
     return out != SP_OK ? out : rc2;
 }
@@ -3030,7 +3125,6 @@ struct sp_batch {
     HostHam ham{};
     std::vector<HostBond> all_bonds;
     int n_shells = 0, shape = -1, shape_ndmi = 0;
-    sp::ShapeCoef<float> C{};
     sp::StepCoef<float> SC{};   // the tiled replicas' step kernel (as the single-engine step)
     sp::Site2D<float> Q{};
     std::vector<BatchRep> reps;
@@ -3184,10 +3278,10 @@ template <int S, int NDMI>
 void batch_launch_resident(sp_batch* b, hipStream_t s, int n_steps) {
     if (b->n_res32)
         hipLaunchKernelGGL((sp::k_batch_resident<float, S, NDMI, 32, 32, 1024>), dim3(b->n_res32), dim3(1024), 0, s,
-                           b->C, b->Q, b->d_reps, b->d_res32, b->d_step, n_steps);
+                           b->SC, b->Q, b->d_reps, b->d_res32, b->d_step, n_steps);
     if (b->n_res64)
         hipLaunchKernelGGL((sp::k_batch_resident<float, S, NDMI, 64, 64, 1024>), dim3(b->n_res64), dim3(1024), 0, s,
-                           b->C, b->Q, b->d_reps, b->d_res64, b->d_step, n_steps);
+                           b->SC, b->Q, b->d_reps, b->d_res64, b->d_step, n_steps);
 }
 
 template <int S, int NDMI, int PER>
@@ -3382,12 +3476,12 @@ int sp_batch_add(sp_batch* b, sp_engine* e, const sp_llg_params* p) {
         b->shape = e->shape;
         b->shape_ndmi = e->shape_ndmi;
         switch (e->shape) {
-            case sp::SH_SQ1: b->C = shape_coef_for<float, sp::SH_SQ1>(e); b->SC = step_coef_for<float, sp::SH_SQ1>(e); break;
-            case sp::SH_SQ2: b->C = shape_coef_for<float, sp::SH_SQ2>(e); b->SC = step_coef_for<float, sp::SH_SQ2>(e); break;
-            case sp::SH_SQ3: b->C = shape_coef_for<float, sp::SH_SQ3>(e); b->SC = step_coef_for<float, sp::SH_SQ3>(e); break;
-            case sp::SH_TRI1: b->C = shape_coef_for<float, sp::SH_TRI1>(e); b->SC = step_coef_for<float, sp::SH_TRI1>(e); break;
-            case sp::SH_TRI2: b->C = shape_coef_for<float, sp::SH_TRI2>(e); b->SC = step_coef_for<float, sp::SH_TRI2>(e); break;
-            default: b->C = shape_coef_for<float, sp::SH_TRI3>(e); b->SC = step_coef_for<float, sp::SH_TRI3>(e); break;
+            case sp::SH_SQ1: b->SC = step_coef_for<float, sp::SH_SQ1>(e); break;
+            case sp::SH_SQ2: b->SC = step_coef_for<float, sp::SH_SQ2>(e); break;
+            case sp::SH_SQ3: b->SC = step_coef_for<float, sp::SH_SQ3>(e); break;
+            case sp::SH_TRI1: b->SC = step_coef_for<float, sp::SH_TRI1>(e); break;
+            case sp::SH_TRI2: b->SC = step_coef_for<float, sp::SH_TRI2>(e); break;
+            default: b->SC = step_coef_for<float, sp::SH_TRI3>(e); break;
         }
         b->Q = make_site2d<float>(e, nullptr);
         b->has_template = true;
