@@ -2152,7 +2152,7 @@ int mc_plan(sp_engine* e) {
                 for (int ic = 0; ic < e->mc_m[2]; ++ic)
                     for (int beta = 0; beta < g.nb; ++beta) {
                         if (e->mc_col[((ia * e->mc_m[1] + ib) * e->mc_m[2] + ic) * g.nb + beta] != colour) continue;
-                        sp::McClass c{{ia, ib, ic}, beta, {0, 0, 0}, (int)block};
+                        sp::McClass c{{ia, ib, ic}, beta, {0, 0, 0}, (int)block, e->bstart[beta], e->bstart[beta + 1]};
                         long long count = 1;
                         for (int k = 0; k < 3; ++k) {
                             c.n[k] = (g.n[k] - c.first[k] + e->mc_m[k] - 1) / e->mc_m[k];
@@ -2212,6 +2212,12 @@ int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t o
     const sp::Phys<double> P = make_phys<double>(e, nullptr);
     sp::McArgs<double> M{};
     for (int q = 0; q < 3; ++q) M.cm[q] = e->mc_m[q];
+    M.near = 1;
+    for (const HostBond& b : e->bonds) {
+        for (int q = 0; q < 3; ++q)
+            if (std::abs(b.d[q]) > e->geo.n[q]) M.near = 0;
+        if (b.D[0] != 0.0 || b.D[1] != 0.0 || b.D[2] != 0.0) M.dmi = 1;
+    }
     M.kT = kKB * p->T_K;
     M.cos_cone = std::cos(p->cone_deg * M_PI / 180.0);
     const bool adaptive = p->target_acceptance > 0.0;
@@ -2232,6 +2238,7 @@ int mc_run_impl(sp_engine* e, const sp_mc_params* p, int64_t n_sweeps, int64_t o
         for (int colour = 0; colour < e->mc_ncol; ++colour) {
             M.cls = cls + e->mc_cls_start[colour];
             M.n_cls = e->mc_cls_start[colour + 1] - e->mc_cls_start[colour];
+            for (int q = 0; q < std::min(M.n_cls, 8); ++q) M.start[q] = e->mc_cls[e->mc_cls_start[colour] + q].block;
             hipLaunchKernelGGL((sp::k_mc_colour<T>), dim3(e->mc_blocks[colour]), dim3((unsigned)e->mc_block), 0,
                                e->stream, L, C, P, M, static_cast<T*>(e->d_n), acc);
         }

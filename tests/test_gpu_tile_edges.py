@@ -1,7 +1,8 @@
 """GPU tests at the edges of the tiled kernels' ranges: frames of the pair
 tiles (ragged tiles, sides below the reach, offsets of half a lattice, open
 axes, frames too large for LDS), the GNEB kernels' tile sides and images per
-workgroup, and replica batches of mixed boundary forms."""
+workgroup, replica batches of mixed boundary forms, and the forms of the
+Monte Carlo pair sums."""
 
 import numpy as np
 import pytest
@@ -152,3 +153,39 @@ def test_batch_of_mixed_boundary_forms_equals_single_engines():
         e.run(0.3, 0.001, 11, T=20.0, seed=5, replica=r)
         assert np.abs(b.get_spins(r) - e.get_spins()).max() <= 1e-6, f"replica {r}"
         e.close()
+
+
+MC_FAR = {   # lattice, pairs within it, and the same pairs written one lattice length further
+    "square12x8": (si.square(12, 8), [((1, 0, 0), 1.0), ((0, 1, 0), 0.7)], (12, 8, 0)),
+    "tri12x6": (si.triangular(12, 6), [((1, 0, 0), 1.0), ((0, 1, 0), 1.0), ((-1, 1, 0), 0.8)], (12, 6, 0)),
+    "cubic6x8x10": (si.simple_cubic(6, 8, 10), [((1, 0, 0), 1.0), ((0, 1, 0), 0.7), ((0, 0, 1), -0.4)], (6, 8, 10)),
+}
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("case", sorted(MC_FAR))
+def test_mc_pair_forms_agree(case, precision):
+    """The same bonds as nearest images without DMI, with a DMI vector too
+    small to reach any sum's last bit, and written one lattice length further
+    (wrapped by the general division): three instances of the pair sums, one
+    chain, bit for bit."""
+    import paper_1901_11350_amd as pk
+
+    announce(f"mc pair forms {case} {precision}")
+    geo, pairs, length = MC_FAR[case]
+    n0 = si.uniform_sphere(geo.n_sites, 4)
+    out = []
+    for form in ("near", "dmi", "far"):
+        D = (0.0, 0.0, 1e-300) if form == "dmi" else (0.0, 0.0, 0.0)
+        off = [tuple(x + (n if form == "far" and x else 0) for x, n in zip(d, length)) for d, _ in pairs]
+        e = pk.Engine(0, precision)
+        e.set_geometry(geo)
+        e.set_hamiltonian(HAM)
+        e.set_pairs([(0, 0, o, J, D) for o, (_, J) in zip(off, pairs)])
+        e.set_spins(n0)
+        _, acc = e.mc_run(8.0, 40.0, 5, seed=3)[:2]
+        out.append((acc, e.get_spins()))
+        e.close()
+    assert 0 < out[0][0] < 5 * geo.n_sites
+    for acc, n in out[1:]:
+        assert acc == out[0][0] and np.array_equal(n, out[0][1])
