@@ -320,7 +320,8 @@ int sp_dipole_gradient_dev(sp_engine *e, const void *n_soa_dev, void *g_soa_dev,
  * passes inputs and outputs as for sp_dipole_gradient_dev (same values, bit
  * for bit, as its SP_DDI_DIRECT result).  SP_E_ARG when the partial sums
  * (3 N x slices values of the engine precision; slices = 16 up to 65,536
- * sites, then about 2^20 / N) exceed 32 MiB, e.g. beyond about 1.4 M sites
+ * sites, then about 2^20 / N; the matrix-unit form takes as many more as
+ * the array holds) exceed 32 MiB, e.g. beyond about 1.4 M sites
  * in FP64 or 2.8 M in FP32.  Every call on a GPU shares that GPU's array:
  * calls that overlap on one GPU (engines on different streams) race and
  * must be ordered by the caller. */
@@ -358,6 +359,8 @@ const char *sp_step_path(const sp_engine *e);
  * (about a second; environment variable SP_PERSIST_SPIN_LIMIT lowers it)
  * makes sp_run return SP_E_HIP with the spins invalid.  sp_llg_step and the
  * other solvers use the one-step kernel of the same tile on that path.
+ * Unless a path was set by name, lattices of at most 1024 sites (FP32: 2048)
+ * on the shape2d path run many steps per launch in one workgroup.
  * A path the current lattice does not allow gives SP_E_UNSUPPORTED, an
  * unknown name SP_E_ARG.  Reset by sp_set_hamiltonian (which picks the
  * default path of the lattice). */

@@ -503,10 +503,9 @@ int dipole_table_setup(sp_engine* e) {
     double* d_geo = nullptr;
     int rc = dalloc(e, d_geo, geo.size() * sizeof(double));
     if (rc) return rc;
-    rc = dalloc(e, e->dd_table, (size_t)noff * (2 * a.Nb - 1) * 6 * a.RL * sizeof(T));
-    if (rc) {
+    if (dalloc(e, e->dd_table, (size_t)noff * (2 * a.Nb - 1) * 6 * a.RL * sizeof(T))) {
         (void)hipFree(d_geo);
-        return rc;
+        return SP_OK;      // no room for the table: the vector form
     }
     hipError_t st = hipMemcpy(d_geo, geo.data(), geo.size() * sizeof(double), hipMemcpyHostToDevice);
     if (st == hipSuccess) {

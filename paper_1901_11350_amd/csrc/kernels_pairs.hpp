@@ -16,7 +16,8 @@
 // replaces on these lattices (k_predict, k_correct, k_gradient,
 // k_observe_partial: three wrapped coordinates, six coupling values and three
 // loads from memory per bond and site) took 63 us per stage on 48^3 sites
-// with 122 bonds and stays for tables whose frame does not fit.
+// with 122 bonds, the tiles take 20; it stays for tables whose frame does not
+// fit.
 #pragma once
 
 #include "kernels_fused2d.hpp"
