@@ -919,7 +919,10 @@ sp::StencilB<T> make_stencilb(const sp_engine* e, int WN, int HN, int PN, int WP
             S.offN[q] = PN * b.bj + b.d[0] + WN * (b.d[1] + HN * b.d[2]);
             S.offP[q] = PP * b.bj + b.d[0] + WP * (b.d[1] + HP * b.d[2]);
             S.J[q] = (T)b.J;
-            for (int c = 0; c < 3; ++c) S.D[q][c] = (T)b.D[c];
+            for (int c = 0; c < 3; ++c) {
+                S.D[q][c] = (T)b.D[c];
+                if (S.D[q][c] != T(0)) S.dmi |= 1u << (q >> 2);
+            }
         }
         for (; q % 4; ++q) {   // zero bonds (the struct is value-initialised)
             S.offN[q] = 0;

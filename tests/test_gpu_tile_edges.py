@@ -54,6 +54,12 @@ PAIRS = {
                          _box((1, 1, 1)) + [(0, 0, (0, 7, 0), 5.0, (1.0, 1.0, 1.0))]),
     "basis19x5x9": (BASIS2_GEO, HAM2, [(0, 1, (0, 0, 0), 0.8, (0.1, 0.0, -0.2)), (1, 0, (2, 1, 0), 0.3, (0.0, 0.2, 0.0)),
                                        (0, 0, (3, 1, 4), -0.2, (0.05, 0.05, 0.05)), (1, 1, (0, 2, -5), 0.5, (0, 0, 0))]),
+    # the fused tile path, DMI in the last group of four bonds of one atom only
+    "basis21x10_late_dmi": (si.Geometry(((1.0, 0, 0), (0, 1.0, 0), (0, 0, 1.0)), ((0, 0, 0), (0.3, 0.4, 0)),
+                                        (21, 10, 1), (1, 0, 0)), HAM2,
+                            [(0, 0, (1, 0, 0), 0.8, (0, 0, 0)), (0, 0, (0, 1, 0), 0.3, (0, 0, 0)),
+                             (0, 1, (0, 0, 0), -0.2, (0, 0, 0)), (0, 1, (1, 0, 0), 0.4, (0, 0, 0)),
+                             (0, 0, (2, 1, 0), 0.1, (0.2, 0.1, -0.3)), (1, 1, (1, 1, 0), 0.5, (0, 0, 0))]),
     # a frame past LDS: the site loop
     "square140x130_far": (si.square(140, 130), HAM, _box((1, 1), 2) + [(0, 0, (62, 1, 0), 0.3, (0.0, 0.1, 0.0)),
                                                                        (0, 0, (3, 61, 0), -0.2, (0.1, 0.0, 0.0))]),
