@@ -195,3 +195,41 @@ def test_mc_pair_forms_agree(case, precision):
     assert 0 < out[0][0] < 5 * geo.n_sites
     for acc, n in out[1:]:
         assert acc == out[0][0] and np.array_equal(n, out[0][1])
+
+
+@pytest.mark.parametrize("n", [(43, 41), (591, 591), (592, 592), (803, 700)])
+def test_readbacks_in_chunks(n):
+    """FP32 spins read back below and above the 2^20 values from which chunks of
+    65,536 are used (591^2 x 3 = 1,047,843, 592^2 x 3 = 1,051,392; the last
+    chunk ragged) and small ones after large ones: every value the one
+    stored."""
+    import paper_1901_11350_amd as pk
+
+    announce(f"readback {n}")
+    geo = si.square(*n)
+    e = pk.Engine(0, "f32")
+    e.set_geometry(geo)
+    e.set_hamiltonian(HAM_SQ)
+    for seed in (1, 2):
+        n0 = si.uniform_sphere(geo.n_sites, seed)
+        e.set_spins(n0)
+        assert np.array_equal(e.get_spins(), n0.astype(np.float32).astype(np.float64))
+    g0 = e.gradient()
+    assert np.array_equal(g0, e.gradient())
+    b = pk.Batch(0)
+    small = si.square(40, 24)
+    s = pk.Engine(0, "f32")
+    s.set_geometry(small)
+    s.set_hamiltonian(HAM_SQ)
+    m0 = si.uniform_sphere(small.n_sites, 3)
+    s.set_spins(m0)
+    for x in (e, s):
+        b.add(x, 0.3, 0.001, T=0.0, seed=5)
+    assert np.array_equal(b.get_spins(1), s.get_spins())     # before the first run
+    b.run(2)
+    big = b.get_spins(0)
+    got = b.get_spins(1)
+    s.step_path = "shape2d/32x16x512"
+    s.run(0.3, 0.001, 2, T=0.0, seed=5)
+    assert np.abs(got - s.get_spins()).max() <= 1e-6
+    assert np.array_equal(big, b.get_spins(0)) and np.isfinite(big).all()
