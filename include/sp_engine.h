@@ -441,7 +441,10 @@ int sp_batch_add_gneb(sp_batch *b, sp_gneb *g);
 /* Chain of n_images (>= 3) images on engine e's lattice and Hamiltonian (no
  * dipole term), in e's precision.  chain: n_images*3N doubles, image-major,
  * each image SoA; spins are normalised on input.  The chain borrows e: e
- * must outlive it and keep its geometry and Hamiltonian. */
+ * must outlive it and keep its lattice.  After another sp_set_hamiltonian or
+ * sp_set_pairs on e the next iterations evaluate every image with it (the
+ * minimiser's previous force is kept); with no Hamiltonian set, or another
+ * number of sites, they return SP_E_ORDER. */
 int sp_gneb_create(sp_gneb **out, sp_engine *e, int n_images, const double *chain, double k_spring,
                    double vp_dt, double vp_mass);
 void sp_gneb_destroy(sp_gneb *c);

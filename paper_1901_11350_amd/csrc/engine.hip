@@ -142,6 +142,7 @@ struct sp_engine {
     double* d_mc_rows = nullptr;        // partial rows of observations not yet reduced
     size_t mc_rows_cap = 0;
     std::string path_label;
+    uint64_t ham_gen = 0;               // counts what replaced the geometry or the Hamiltonian
 
     size_t esz() const { return precision == SP_F64 ? 8 : 4; }
 
@@ -293,6 +294,7 @@ void drop_graphs(sp_engine* e) {
 
 void free_state_buffers(sp_engine* e) {
     drop_graphs(e);
+    ++e->ham_gen;
     // the Monte Carlo plan belongs to the bonds
     e->mc_ncol = 0;
     dfree(e->d_mc);
@@ -3169,7 +3171,10 @@ struct sp_gneb {
     HostStage stage;
     int device = 0;
     int M = 0, N = 0, nblk = 0, nblk_e = 0;
+    bool tiled = false;      // gradient on tiles (k_gneb_grad_tile), else on blocks of 256 sites
     int tile = 16;           // side of the gradient tiles (16 or 32)
+    size_t epart_cap = 0;    // energy partials allocated
+    uint64_t ham_gen = 0;    // the engine's generation that the layout and the endpoints belong to
     int ipw = 1;             // images per workgroup of the tangent and force kernels (1, 2 or 4)
     double k = 1.0, dt = 0.1, m = 1.0;
     void *x = nullptr, *x2 = nullptr, *F = nullptr, *g = nullptr;   // chain, the chain's other buffer, force, gradient
@@ -3230,6 +3235,7 @@ namespace {
 
 template <typename T>
 int gneb_enqueue(sp_gneb* G, int n_iter, hipStream_t st, double tol = 0.0);
+int gneb_follow(sp_gneb* G, hipStream_t st);
 
 int bfail(sp_batch* b, int code, const std::string& msg) {
     if (b) b->err = msg;
@@ -3451,6 +3457,13 @@ int batch_capture(sp_batch* b) {
 
 int batch_advance(sp_batch* b, int64_t n_steps, bool use_graph) {
     int64_t left = n_steps;
+    if (b->gneb && n_steps > 0 && b->gneb->ham_gen != b->gneb->e->ham_gen) {
+        // the captured chunk launches the chain with the engine's earlier Hamiltonian
+        BHIPCHK(b, hipStreamSynchronize(b->stream));
+        batch_drop_graphs(b);
+        const int rc = gneb_follow(b->gneb, b->stream);
+        if (rc) return bfail(b, rc, b->gneb->err);
+    }
     while (use_graph && left >= b->chunk) {
         if (!b->gexec || b->g_parity != b->parity || b->g_cfg != b->cfg || b->g_chunk != b->chunk ||
             (b->gneb != nullptr) != (b->gexec_chain != nullptr) || (b->gneb && b->g_chain_x != b->gneb->x)) {
@@ -3710,11 +3723,30 @@ int gfail(sp_gneb* G, int code, const std::string& msg) {
     return code;
 }
 
-// Images on the stencil path whose sides divide into the 64 x 4 tiles of
-// k_gneb_grad_shape (then tiles and site blocks coincide in number).
-bool gneb_tiles(const sp_gneb* G) {
+// Layout of the gradient kernel and of its energy partials for the engine's
+// present Hamiltonian: tiles where it has a compile-time 2D stencil (32 x 32
+// sites while 256 workgroups are left, else 16 x 16), blocks of 256 sites
+// elsewhere.  The partials grow with the layout.
+int gneb_layout(sp_gneb* G) {
     const sp_engine* e = G->e;
-    return e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0;
+    G->tiled = e->shape >= 0 && !e->ham.ddi && e->ham.n_gauss == 0;
+    auto tiles = [&](int side) { return ((e->geo.n[0] + side - 1) / side) * ((e->geo.n[1] + side - 1) / side); };
+    G->tile = (long long)tiles(32) * (G->M - 2) >= 256 ? 32 : 16;
+    G->nblk_e = G->tiled ? tiles(G->tile) : G->nblk;
+    G->ham_gen = e->ham_gen;
+    const size_t need = (size_t)G->M * G->nblk_e;
+    if (need > G->epart_cap) {
+        if (G->epart) (void)hipFree(G->epart);   // waits for the launches that use it
+        G->epart = nullptr;
+        G->epart_cap = 0;
+        if (hipMalloc((void**)&G->epart, need * sizeof(double)) != hipSuccess) {
+            (void)hipGetLastError();
+            G->ham_gen = 0;                      // no generation: the next call tries again
+            return gfail(G, SP_E_NOMEM, "GNEB allocation failed");
+        }
+        G->epart_cap = need;
+    }
+    return SP_OK;
 }
 
 sp::GnebDims gneb_dims(const sp_gneb* G) { return sp::GnebDims{G->M, G->N, G->nblk, G->nblk_e}; }
@@ -3765,14 +3797,14 @@ void gneb_grad_shape(sp_gneb* G, hipStream_t st, bool move, const int* stop) {
     }
 }
 
-// One evaluation of the forces, after the position step when `move` (an
-// iteration: the partials then also hold the velocity that follows).
+// Gradient and energies of every image, or, after the position step when
+// `move`, of the interior images.
 template <typename T>
-int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr) {
+void gneb_gradient(sp_gneb* G, bool move, hipStream_t st, const int* stop) {
     sp_engine* e = G->e;
     const sp::GnebDims d = gneb_dims(G);
     const bool apart = gneb_sum_apart(G);
-    if (gneb_tiles(G)) {
+    if (G->tiled) {
         switch (e->shape) {
             case sp::SH_SQ1: gneb_grad_shape<T, sp::SH_SQ1>(G, st, move, stop); break;
             case sp::SH_SQ2: gneb_grad_shape<T, sp::SH_SQ2>(G, st, move, stop); break;
@@ -3790,6 +3822,15 @@ int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr
                            make_lattice(e), make_coef64(e), make_phys<double>(e, nullptr),
                            static_cast<const T*>(G->x), static_cast<T*>(G->g), G->epart, move ? 1 : 0, stop);
     }
+}
+
+// One evaluation of the forces, after the position step when `move` (an
+// iteration: the partials then also hold the velocity that follows).
+template <typename T>
+int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr) {
+    const sp::GnebDims d = gneb_dims(G);
+    const bool apart = gneb_sum_apart(G);
+    gneb_gradient<T>(G, move, st, stop);
     const T* x = static_cast<const T*>(G->x);
     const T* g = static_cast<const T*>(G->g);
     auto launch = [&](auto ipw) {
@@ -3808,6 +3849,24 @@ int gneb_forces(sp_gneb* G, bool move, hipStream_t st, const int* stop = nullptr
     if (apart)
         hipLaunchKernelGGL((sp::k_gneb_sum<2>), dim3(1), dim3(256), 0, st, G->part, gneb_parts(G), G->vf, stop);
     hipError_t s = hipGetLastError();
+    if (s != hipSuccess) return gfail(G, SP_E_HIP, hipGetErrorString(s));
+    return SP_OK;
+}
+
+// Before iterations: a chain whose engine was given another Hamiltonian since
+// the last ones takes the layout of the new one, and all its images, the fixed
+// ones among them, their gradient and energy.  (Iterations evaluate the
+// interior images only.)
+int gneb_follow(sp_gneb* G, hipStream_t st) {
+    const sp_engine* e = G->e;
+    if (G->ham_gen == e->ham_gen) return SP_OK;
+    if (!e->has_ham || e->N != G->N)
+        return gfail(G, SP_E_ORDER, "the chain's engine has no Hamiltonian or another number of sites");
+    const int rc = gneb_layout(G);
+    if (rc) return rc;
+    if (e->precision == SP_F64) gneb_gradient<double>(G, false, st, nullptr);
+    else gneb_gradient<float>(G, false, st, nullptr);
+    const hipError_t s = hipGetLastError();
     if (s != hipSuccess) return gfail(G, SP_E_HIP, hipGetErrorString(s));
     return SP_OK;
 }
@@ -3910,12 +3969,8 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
     G->m = vp_mass;
     (void)hipSetDevice(e->device);
     const size_t vb = (size_t)G->M * 3 * G->N * e->esz();
-    // gradient tiles of 32 x 32 sites while 256 workgroups are left, else 16 x
-    // 16 (blocks of 256 without tiles); up to four images per workgroup in
-    // the other two kernels while 256 workgroups are left
-    auto tiles = [&](int side) { return ((e->geo.n[0] + side - 1) / side) * ((e->geo.n[1] + side - 1) / side); };
-    if ((long long)tiles(32) * (G->M - 2) >= 256) G->tile = 32;
-    G->nblk_e = gneb_tiles(G) ? tiles(G->tile) : G->nblk;
+    // up to four images per workgroup in the tangent and force kernels while
+    // 256 workgroups are left
     G->ipw = 4;
     while (G->ipw > 1 && (long long)G->nblk * gneb_groups(G->M - 2, G->ipw) < 256) G->ipw /= 2;
     const size_t parts = (size_t)(G->M - 2) * G->nblk * 2;
@@ -3923,7 +3978,7 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
     for (void** b : bufs)
         if (hipMalloc(b, vb) != hipSuccess) { gneb_free(G); delete G; return fail(e, SP_E_NOMEM, "GNEB allocation failed"); }
     if (hipMalloc((void**)&G->part, parts * sizeof(double)) != hipSuccess ||
-        hipMalloc((void**)&G->epart, (size_t)G->M * G->nblk_e * sizeof(double)) != hipSuccess ||
+        gneb_layout(G) != SP_OK ||
         hipMalloc((void**)&G->tpart, (size_t)G->M * G->nblk * 3 * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->E, G->M * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&G->s3, 3 * G->M * sizeof(double)) != hipSuccess ||
@@ -3997,7 +4052,9 @@ int sp_gneb_iterate(sp_gneb* G, int n_iter) {
     if (n_iter < 0) return gfail(G, SP_E_ARG, "n_iter must be >= 0");
     if (G->batch) return gfail(G, SP_E_ORDER, "the chain is attached to a batch: sp_batch_run advances it");
     (void)hipSetDevice(G->e->device);
-    const int rc = G->e->precision == SP_F64 ? gneb_iterate<double>(G, n_iter) : gneb_iterate<float>(G, n_iter);
+    int rc = n_iter > 0 ? gneb_follow(G, G->e->stream) : SP_OK;
+    if (rc) return rc;
+    rc = G->e->precision == SP_F64 ? gneb_iterate<double>(G, n_iter) : gneb_iterate<float>(G, n_iter);
     if (rc) return rc;
     if (hipStreamSynchronize(G->e->stream) != hipSuccess) return gfail(G, SP_E_HIP, "synchronisation failed");
     return SP_OK;
@@ -4010,8 +4067,10 @@ int sp_gneb_iterate_tol(sp_gneb* G, int max_iter, double tol, int* iters_done) {
     if (!(tol > 0.0) || !std::isfinite(tol)) return gfail(G, SP_E_ARG, "tol must be finite and > 0");
     if (G->batch) return gfail(G, SP_E_ORDER, "the chain is attached to a batch: sp_batch_run advances it");
     (void)hipSetDevice(G->e->device);
-    const int rc = G->e->precision == SP_F64 ? gneb_enqueue<double>(G, max_iter, G->e->stream, tol)
-                                             : gneb_enqueue<float>(G, max_iter, G->e->stream, tol);
+    int rc = max_iter > 0 ? gneb_follow(G, G->e->stream) : SP_OK;
+    if (rc) return rc;
+    rc = G->e->precision == SP_F64 ? gneb_enqueue<double>(G, max_iter, G->e->stream, tol)
+                                   : gneb_enqueue<float>(G, max_iter, G->e->stream, tol);
     if (rc) return rc;
     int st[2] = {0, -1};
     if (max_iter > 0 &&
@@ -4020,7 +4079,7 @@ int sp_gneb_iterate_tol(sp_gneb* G, int max_iter, double tol, int* iters_done) {
         return gfail(G, SP_E_HIP, "synchronisation failed");
     const int done = st[0] ? st[1] + 1 : max_iter;
     // the skipped iterations swapped the chain's buffers on the host only
-    if (gneb_tiles(G) && (max_iter - done) % 2) std::swap(G->x, G->x2);
+    if (G->tiled && (max_iter - done) % 2) std::swap(G->x, G->x2);
     G->iterations += done;
     if (iters_done) *iters_done = done;
     return SP_OK;
