@@ -3916,7 +3916,8 @@ int gneb_upload(sp_gneb* G, const double* chain) {
             h[im * L + G->N + i] = (T)(y / r);
             h[im * L + 2 * G->N + i] = (T)(z / r);
         }
-    if (hipMemcpy(G->x, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
+    if (hipMemcpyAsync(G->x, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, G->e->stream) != hipSuccess ||
+        hipStreamSynchronize(G->e->stream) != hipSuccess)
         return gfail(G, SP_E_HIP, "chain upload failed");
     return SP_OK;
 }
@@ -3991,16 +3992,17 @@ int sp_gneb_create(sp_gneb** out, sp_engine* e, int n_images, const double* chai
         delete G;
         return fail(e, SP_E_NOMEM, "GNEB allocation failed");
     }
-    if (hipMemset(G->F, 0, vb) != hipSuccess || hipMemset(G->scale, 0, sizeof(double)) != hipSuccess ||
-        hipMemset(G->vf, 0, 2 * sizeof(double)) != hipSuccess || hipMemset(G->types, 0, G->M * sizeof(int)) != hipSuccess ||
-        hipMemset(G->stop, 0, 2 * sizeof(int)) != hipSuccess) {
+    // on the engine's stream, which is not ordered after the null stream
+    auto clear = [&](void* p, size_t bytes) { return hipMemsetAsync(p, 0, bytes, e->stream) == hipSuccess; };
+    if (!clear(G->F, vb) || !clear(G->scale, sizeof(double)) || !clear(G->vf, 2 * sizeof(double)) ||
+        !clear(G->types, G->M * sizeof(int)) || !clear(G->stop, 2 * sizeof(int))) {
         gneb_free(G);
         delete G;
         return fail(e, SP_E_HIP, "GNEB initialisation failed");
     }
     rc = e->precision == SP_F64 ? gneb_upload<double>(G, chain) : gneb_upload<float>(G, chain);
     // the endpoints have to stand in both chain buffers
-    if (rc == SP_OK && hipMemcpy(G->x2, G->x, vb, hipMemcpyDeviceToDevice) != hipSuccess)
+    if (rc == SP_OK && hipMemcpyAsync(G->x2, G->x, vb, hipMemcpyDeviceToDevice, e->stream) != hipSuccess)
         rc = gfail(G, SP_E_HIP, "chain copy failed");
     if (rc == SP_OK)
         rc = e->precision == SP_F64 ? gneb_forces<double>(G, false, e->stream) : gneb_forces<float>(G, false, e->stream);
