@@ -657,6 +657,8 @@ int launch_dipole(sp_engine* e, const void* n, void* gdd) {
 // times the workgroups that LDS leaves short of four per CU.  The form is left to the site loop when no frame fits, or when
 // staging would move more cells than the bonds read (a few bonds of long
 // reach).
+constexpr int kPairLds = 158 * 1024;   // LDS of a workgroup at most
+
 template <typename T>
 int pair_setup(sp_engine* e) {
     e->pair_ok = false;
@@ -748,12 +750,14 @@ int pair_setup(sp_engine* e) {
     if (db) std::memcpy(both.data() + jb, D.data(), db);
     if (jb + db) HIPCHK(e, hipMemcpy(e->d_pairs, both.data(), jb + db, hipMemcpyHostToDevice));
     const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>) + jb + db);
-    if (bytes > 158 * 1024) return SP_OK;
+    if (bytes > kPairLds) return SP_OK;
     if (bytes > 48 * 1024) {
+        // the limit belongs to the kernels, which every engine launches with
+        // LDS of its own size: always the largest
         const void* fn[] = {(const void*)sp::k_pair_tile<T, sp::PAIR_GRADIENT>, (const void*)sp::k_pair_tile<T, sp::PAIR_PREDICT>,
                             (const void*)sp::k_pair_tile<T, sp::PAIR_CORRECT>, (const void*)sp::k_pair_tile<T, sp::PAIR_OBSERVE>};
         for (const void* f : fn)
-            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kPairLds) != hipSuccess) {
                 (void)hipGetLastError();
                 return SP_OK;      // the site loop stays
             }
