@@ -93,8 +93,9 @@ struct RunGraph {
     hipGraphExec_t exec;
 };
 
-// Pinned chunks of a readback (download_widened).
+// Pinned chunks of a readback (download_widened), one reader's at a time.
 struct HostStage {
+    std::mutex busy;
     float* p[2] = {nullptr, nullptr};
     hipEvent_t ev[2] = {nullptr, nullptr};
 };
@@ -215,7 +216,8 @@ int fail(sp_engine* e, int code, const std::string& msg) {
 // copy of the next: 3.1M values 1627 -> 1104 us, the first read 4471 -> 1922.
 // Pinning takes 0.3 ms once, so arrays below a million values, whose first
 // read would be the slower (786,432: 375 -> 705 us, then 371 -> 287), keep the
-// pageable copy unless the chunks are there.
+// pageable copy unless the chunks are there, and so does a reader that finds
+// them in another thread's hands.
 constexpr size_t kStageFloats = 65536, kStageFrom = 1 << 20;
 
 hipError_t download_pageable(hipStream_t st, const float* src, double* dst, size_t n) {
@@ -237,7 +239,12 @@ void stage_free(HostStage& h) {
 }
 
 hipError_t download_widened(HostStage& h, hipStream_t st, const float* src, double* dst, size_t n) {
-    if (n < kStageFrom && !(h.ev[0] && h.ev[1])) return download_pageable(st, src, dst, n);
+    std::unique_lock<std::mutex> own(h.busy, std::try_to_lock);
+    if (!own.owns_lock()) return download_pageable(st, src, dst, n);
+    if (n < kStageFrom && !(h.ev[0] && h.ev[1])) {
+        own.unlock();
+        return download_pageable(st, src, dst, n);
+    }
     for (int k = 0; k < 2; ++k)
         if ((!h.p[k] && hipHostMalloc((void**)&h.p[k], kStageFloats * sizeof(float), hipHostMallocDefault) != hipSuccess) ||
             (!h.ev[k] && hipEventCreateWithFlags(&h.ev[k], hipEventDisableTiming) != hipSuccess)) {
