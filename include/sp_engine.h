@@ -318,7 +318,9 @@ int sp_dipole_gradient_dev(sp_engine *e, const void *n_soa_dev, void *g_soa_dev,
  * with its partial sums in a file-scope device array of 32 MiB per GPU
  * instead of engine memory; it calls no allocating routine.  The caller
  * passes inputs and outputs as for sp_dipole_gradient_dev (same values, bit
- * for bit, as its SP_DDI_DIRECT result).  SP_E_ARG when the partial sums
+ * for bit, as its SP_DDI_DIRECT result; an engine in SP_DDI_FFT mode keeps no
+ * interaction table and sums in the form without one, the same field to
+ * rounding).  SP_E_ARG when the partial sums
  * (3 N x slices values of the engine precision; slices = 16 up to 65,536
  * sites, then about 2^20 / N; the matrix-unit form takes as many more as
  * the array holds) exceed 32 MiB, e.g. beyond about 1.4 M sites

@@ -2605,7 +2605,8 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
         e->dd_slices = std::max(1, std::min(16, (2048 * 256 * 2) / std::max(e->N, 1)));
         e->dd_slices = std::min(e->dd_slices, tiles);
         if ((rc = dalloc(e, e->d_gdd, vbytes)) || (rc = dalloc(e, e->d_gddp, vbytes)) ||
-            (rc = DISPATCH(e, dipole_table_setup, e)) ||
+            // the fields of FFT mode never read the table
+            (H.ddi != SP_DDI_FFT && (rc = DISPATCH(e, dipole_table_setup, e))) ||
             (rc = dalloc(e, e->d_ddpart, vbytes * dipole_slices(e)))) {
             free_state_buffers(e);
             e->has_ham = false;
