@@ -182,14 +182,16 @@ __device__ __forceinline__ double dd_kernel_value(const FftDims& d, const double
 }
 
 // Half spectra along a of the real channels 2q, 2q + 1 (q = blockIdx.y) on
-// ROWS rows b.  KERNEL = false: mu_p n, channel 3p + component, Nb rows.
+// ROWS rows b; (ka, channel, b) lies at ka ka_pitch + channel ch_pitch + b.
+// KERNEL = false: mu_p n, channel 3p + component, Nb rows.
 // KERNEL = true: the kernel tensor, channel 6 offset + component, Lb rows.
 // With the complex line Z = X0 + i X1: X0^(k) = (Z^(k) + conj Z^(-k)) / 2,
 // X1^(k) = (Z^(k) - conj Z^(-k)) / (2i).
 template <typename T, int LOGL, bool KERNEL>
 __global__ void __launch_bounds__((FftLine<T, LOGL>::NT))
-    k_dd_rows(FftDims d, int channels, int rows, const T* __restrict__ n, const T* __restrict__ mu_plane,
-              const double* __restrict__ geo, const Cx<T>* __restrict__ tw, Cx<T>* __restrict__ X) {
+    k_dd_rows(FftDims d, int channels, int rows, long long ka_pitch, long long ch_pitch, const T* __restrict__ n,
+              const T* __restrict__ mu_plane, const double* __restrict__ geo, const Cx<T>* __restrict__ tw,
+              Cx<T>* __restrict__ X) {
     using F = FftLine<T, LOGL>;
     constexpr int L = F::L, NT = F::NT;
     __shared__ Cx<T> buf[F::ROWS * F::PITCH];
@@ -236,9 +238,9 @@ __global__ void __launch_bounds__((FftLine<T, LOGL>::NT))
         if (b0 + r >= rows) continue;
         const Cx<T> zk = buf[r * F::PITCH + fft_at(ka)];
         const Cx<T> zm = buf[r * F::PITCH + fft_at((L - ka) & (L - 1))];
-        Cx<T>* o = X + ((long long)ka * channels + c0) * rows + b0 + r;
+        Cx<T>* o = X + ka * ka_pitch + c0 * ch_pitch + b0 + r;
         o[0] = Cx<T>{T(0.5) * (zk.re + zm.re), T(0.5) * (zk.im - zm.im)};
-        if (c1 < channels) o[rows] = Cx<T>{T(0.5) * (zk.im + zm.im), T(-0.5) * (zk.re - zm.re)};
+        if (c1 < channels) o[ch_pitch] = Cx<T>{T(0.5) * (zk.im + zm.im), T(-0.5) * (zk.re - zm.re)};
     }
 }
 
@@ -273,19 +275,18 @@ __global__ void __launch_bounds__(256) k_dd_lines(const Cx<T>* in, int n_in, Cx<
 
 // Output channel spectra of one frequency:
 //   G_{3p+alpha} = sum_{p', beta} W^_{p p'}^{alpha beta} X_{3p'+beta}
-// W^ layout: [ka][offset][sym6][kb].  One thread per output channel (y) and
-// frequency.
+// All of them lie frequency (ka, kb) fastest, W^ as [offset][sym6][ka][kb], so
+// that a wavefront reads whole lines however short the columns are.  One
+// thread per output channel (y) and frequency.
 template <typename T>
 __global__ void __launch_bounds__(256) k_dd_mix(FftDims d, const Cx<T>* __restrict__ What,
                                                 const Cx<T>* __restrict__ X, Cx<T>* __restrict__ G) {
     const int F = d.Ka * d.Lb, f = blockIdx.x * 256 + threadIdx.x;
     if (f >= F) return;
-    const int ka = f / d.Lb, kb = f - ka * d.Lb;
     const int ch = blockIdx.y, p = ch / 3, alpha = ch - 3 * p;
     const int c = p % d.Nc, beta = p / d.Nc;
-    const int C3 = 3 * d.P, noff = d.Nc * d.Nbas * d.Nbas;
-    const Cx<T>* W = What + (long long)ka * noff * 6 * d.Lb + kb;
-    const Cx<T>* x = X + (long long)ka * C3 * d.Lb + kb;
+    const Cx<T>* W = What + f;
+    const Cx<T>* x = X + f;
     Cx<T> acc{T(0), T(0)};
     for (int p2 = 0; p2 < d.P; ++p2) {
         const int dc = p2 % d.Nc - c, beta2 = p2 / d.Nc;
@@ -293,14 +294,14 @@ __global__ void __launch_bounds__(256) k_dd_mix(FftDims d, const Cx<T>* __restri
         const T sign = dc >= 0 ? T(1) : T(-1);
 #pragma unroll
         for (int bc = 0; bc < 3; ++bc) {
-            Cx<T> w = W[(long long)(off * 6 + sym6(alpha, bc)) * d.Lb];
+            Cx<T> w = W[(long long)(off * 6 + sym6(alpha, bc)) * F];
             w.im *= sign;
-            const Cx<T> v = x[(long long)(3 * p2 + bc) * d.Lb];
+            const Cx<T> v = x[(long long)(3 * p2 + bc) * F];
             acc.re += w.re * v.re - w.im * v.im;
             acc.im += w.re * v.im + w.im * v.re;
         }
     }
-    G[((long long)ka * C3 + ch) * d.Lb + kb] = acc;
+    G[(long long)ch * F + f] = acc;
 }
 
 // Workgroup size of the fused column kernel: one (frequency, output
@@ -467,9 +468,9 @@ __global__ void __launch_bounds__((FftLine<T, LOGL>::NT))
         const int r = u % F::ROWS, ka = u / F::ROWS;
         Cx<T> g0{T(0), T(0)}, g1{T(0), T(0)};
         if (b0 + r < d.Nb) {
-            const Cx<T>* g = G + ((long long)ka * C3 + c0) * d.Nb + b0 + r;
+            const Cx<T>* g = G + ((long long)c0 * d.Ka + ka) * d.Nb + b0 + r;
             g0 = g[0];
-            if (two) g1 = g[d.Nb];
+            if (two) g1 = g[(long long)d.Ka * d.Nb];
         }
         if (ka > 0 && ka < L / 2)
             buf[r * F::PITCH + fft_at(L - ka)] = Cx<T>{g0.re + g1.im, g1.re - g0.im};
