@@ -3223,7 +3223,7 @@ struct sp_batch {
     size_t arena_floats = 0;
     sp::ReplicaDesc<float>* d_reps = nullptr;
     sp::BatchWork<float>* d_work = nullptr;   // tiles of the tiled replicas
-    int form_start[4] = {0, 0, 0, 0};         // first tile of each boundary form (kernels_fused2d.hpp)
+    int form = 0;                             // boundary form of their instance (kernels_fused2d.hpp)
     int n_work = 0;
     int* d_res32 = nullptr;
     int* d_res64 = nullptr;
@@ -3276,8 +3276,15 @@ void batch_drop_graphs(sp_batch* b) {
 int batch_build_work(sp_batch* b) {
     const TileCfg& tc = kBatchCfgs[b->cfg];
     std::vector<sp::ReplicaDesc<float>> desc(b->reps.size());
-    std::vector<sp::BatchWork<float>> work, by_form[3];
+    std::vector<sp::BatchWork<float>> work;
     std::vector<int> r32, r64;
+    // The tiles of all replicas go in one launch per step, in the weakest
+    // boundary form among them: a launch per form is one after another on the
+    // stream (replicas of 128^2, periodic 96 x 80 and open 75 x 70: 10.0 us per
+    // step in three launches, 3.9 in one; 512^2 with two others 15.7 and 10.5).
+    b->form = 2;
+    for (const BatchRep& R : b->reps)
+        if (!R.resident) b->form = std::min(b->form, boundary_form(R.na, R.nb, R.per_a, R.per_b));
     for (size_t r = 0; r < b->reps.size(); ++r) {
         const BatchRep& R = b->reps[r];
         sp::ReplicaDesc<float>& D = desc[r];
@@ -3303,17 +3310,10 @@ int batch_build_work(sp_batch* b) {
             r64.push_back((int)r);
         } else {
             const int tiles_y = (R.nb + tc.TY - 1) / tc.TY;
-            // a replica takes the boundary form it has as an engine of its own
-            auto& to = by_form[boundary_form(R.na, R.nb, R.per_a, R.per_b)];
             for (int t = 0; t < D.tiles_x * tiles_y; ++t)
-                to.push_back(sp::BatchWork<float>{D, (t % D.tiles_x) * tc.TX, (t / D.tiles_x) * tc.TY});
+                work.push_back(sp::BatchWork<float>{D, (t % D.tiles_x) * tc.TX, (t / D.tiles_x) * tc.TY});
         }
     }
-    for (int f = 0; f < 3; ++f) {
-        b->form_start[f] = (int)work.size();
-        work.insert(work.end(), by_form[f].begin(), by_form[f].end());
-    }
-    b->form_start[3] = (int)work.size();
     void* p = b->d_reps; dfree(p); b->d_reps = nullptr;
     p = b->d_work; dfree(p); b->d_work = nullptr;
     p = b->d_res32; dfree(p); b->d_res32 = nullptr;
@@ -3377,22 +3377,22 @@ void batch_launch_resident(sp_batch* b, hipStream_t s, int n_steps) {
 
 template <int S, int NDMI, int PER>
 void batch_launch_form(sp_batch* b, hipStream_t s, int k, int parity) {
-    const int n = b->form_start[PER + 1] - b->form_start[PER];
-    if (n == 0) return;
-    const auto* work = b->d_work + b->form_start[PER];
     if (b->cfg == 1)
-        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 64, 16, 1024, PER>), dim3(n), dim3(1024), 0, s, b->SC,
-                           b->Q, work, b->d_step, k, parity);
+        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 64, 16, 1024, PER>), dim3(b->n_work), dim3(1024), 0, s,
+                           b->SC, b->Q, b->d_work, b->d_step, k, parity);
     else
-        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 32, 16, 512, PER>), dim3(n), dim3(512), 0, s, b->SC, b->Q,
-                           work, b->d_step, k, parity);
+        hipLaunchKernelGGL((sp::k_batch_tiled<float, S, NDMI, 32, 16, 512, PER>), dim3(b->n_work), dim3(512), 0, s,
+                           b->SC, b->Q, b->d_work, b->d_step, k, parity);
 }
 
 template <int S, int NDMI>
 void batch_launch_tiled(sp_batch* b, hipStream_t s, int k, int parity) {
-    batch_launch_form<S, NDMI, 0>(b, s, k, parity);
-    batch_launch_form<S, NDMI, 1>(b, s, k, parity);
-    batch_launch_form<S, NDMI, 2>(b, s, k, parity);
+    if (!b->n_work) return;
+    switch (b->form) {
+        case 0: batch_launch_form<S, NDMI, 0>(b, s, k, parity); break;
+        case 1: batch_launch_form<S, NDMI, 1>(b, s, k, parity); break;
+        default: batch_launch_form<S, NDMI, 2>(b, s, k, parity);
+    }
 }
 
 template <int S>

@@ -1,0 +1,64 @@
+"""GPU tests of choices between kernels that give the same results: each
+compares the time of the choice taken with a form of the same work that
+cannot take the other one, with room for the spread of short timings."""
+
+import time
+
+import pytest
+
+import spin_inputs as si
+from gpu_util import announce, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+HAM_SQ = si.WORKLOADS["square32_fp64"].hamiltonian
+HAM_TRI = si.WORKLOADS["triangular512_sllg"].hamiltonian
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def _best(call, repeats=9, inner=1):
+    call()
+    times = []
+    for _ in range(repeats):
+        t0 = time.perf_counter()
+        for _ in range(inner):
+            call()
+        times.append((time.perf_counter() - t0) / inner)
+    return min(times)
+
+
+def _batch_time(geos):
+    import torch
+
+    import paper_1901_11350_amd as pk
+
+    b = pk.Batch(0)
+    for r, geo in enumerate(geos):
+        e = pk.Engine(0, "f32")
+        e.set_geometry(geo)
+        e.set_hamiltonian(HAM_SQ)
+        e.set_spins(si.uniform_sphere(e.N, r))
+        b.add(e, 0.3, 0.001, T=0.0, seed=5, replica=r)
+        e.close()
+
+    def run():
+        b.run(256)
+        torch.cuda.synchronize()
+
+    t = _best(run)
+    b.close()
+    return t
+
+
+def test_mixed_batch_steps_in_one_launch():
+    """Three small replicas of different boundary forms (power-of-two sides,
+    periodic, open) step in about the time of three open ones: launches one
+    after another took 2.6 times as long."""
+    announce("mixed batch launches")
+    mixed = [si.square(128, 128), si.square(96, 80), si.square(75, 70, periodic=(0, 1, 0))]
+    alike = [si.square(128, 128, periodic=(0, 1, 0)), si.square(96, 80, periodic=(0, 1, 0)), mixed[2]]
+    assert _batch_time(mixed) < 1.6 * _batch_time(alike)
