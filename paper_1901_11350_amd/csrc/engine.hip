@@ -3229,7 +3229,7 @@ struct sp_batch {
     size_t arena_floats = 0;
     sp::ReplicaDesc<float>* d_reps = nullptr;
     sp::BatchWork<float>* d_work = nullptr;   // tiles of the tiled replicas
-    int form = 0;                             // boundary form of their instance (kernels_fused2d.hpp)
+    int form = 0;                             // their boundary form, or kMixedForms (kernels_fused2d.hpp)
     int n_work = 0;
     int* d_res32 = nullptr;
     int* d_res64 = nullptr;
@@ -3284,13 +3284,12 @@ int batch_build_work(sp_batch* b) {
     std::vector<sp::ReplicaDesc<float>> desc(b->reps.size());
     std::vector<sp::BatchWork<float>> work;
     std::vector<int> r32, r64;
-    // The tiles of all replicas go in one launch per step, in the weakest
-    // boundary form among them: a launch per form is one after another on the
-    // stream (replicas of 128^2, periodic 96 x 80 and open 75 x 70: 10.0 us per
-    // step in three launches, 3.9 in one; 512^2 with two others 15.7 and 10.5).
-    b->form = 2;
-    for (const BatchRep& R : b->reps)
-        if (!R.resident) b->form = std::min(b->form, boundary_form(R.na, R.nb, R.per_a, R.per_b));
+    // The tiles of all replicas go in one launch per step, each in the boundary
+    // form that its replica has as an engine of its own: a launch per form is
+    // one after another on the stream (replicas of 128^2, periodic 96 x 80 and
+    // open 75 x 70: 10.0 us per step in three launches, 3.7 in one; 512^2 with
+    // two others 15.7 and 10.1).
+    b->form = -1;
     for (size_t r = 0; r < b->reps.size(); ++r) {
         const BatchRep& R = b->reps[r];
         sp::ReplicaDesc<float>& D = desc[r];
@@ -3316,8 +3315,10 @@ int batch_build_work(sp_batch* b) {
             r64.push_back((int)r);
         } else {
             const int tiles_y = (R.nb + tc.TY - 1) / tc.TY;
+            const int form = boundary_form(R.na, R.nb, R.per_a, R.per_b);
+            b->form = b->form < 0 || b->form == form ? form : sp::kMixedForms;
             for (int t = 0; t < D.tiles_x * tiles_y; ++t)
-                work.push_back(sp::BatchWork<float>{D, (t % D.tiles_x) * tc.TX, (t / D.tiles_x) * tc.TY});
+                work.push_back(sp::BatchWork<float>{D, (t % D.tiles_x) * tc.TX, (t / D.tiles_x) * tc.TY, form});
         }
     }
     void* p = b->d_reps; dfree(p); b->d_reps = nullptr;
@@ -3397,7 +3398,8 @@ void batch_launch_tiled(sp_batch* b, hipStream_t s, int k, int parity) {
     switch (b->form) {
         case 0: batch_launch_form<S, NDMI, 0>(b, s, k, parity); break;
         case 1: batch_launch_form<S, NDMI, 1>(b, s, k, parity); break;
-        default: batch_launch_form<S, NDMI, 2>(b, s, k, parity);
+        case 2: batch_launch_form<S, NDMI, 2>(b, s, k, parity); break;
+        default: batch_launch_form<S, NDMI, sp::kMixedForms>(b, s, k, parity);
     }
 }
 

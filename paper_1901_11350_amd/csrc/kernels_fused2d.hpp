@@ -674,10 +674,14 @@ template <typename T>
 struct BatchWork {
     ReplicaDesc<T> r;
     int x0, y0;
+    int form;            // boundary form (PER)
 };
 
+constexpr int kMixedForms = 3;   // PER of a batch whose tiles have different forms
+
 // One Depondt step of every tile of every tiled replica: work item
-// (replica, tile) per workgroup.  The step number is *step_base + k, so a
+// (replica, tile) per workgroup, in the form PER or, with kMixedForms, each in
+// its own.  The step number is *step_base + k, so a
 // captured graph of k = 0..K-1 can be replayed after step_base advances.
 template <typename T, int S, int NDMI, int TX, int TY, int NT, int PER>
 __global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, const BatchWork<T>* __restrict__ work,
@@ -690,7 +694,17 @@ __global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, 
     const bool odd = (parity ^ (k & 1)) != 0;
     T* const b0 = W.r.n[0];
     T* const b1 = W.r.n[1];
-    fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, PER>(C, Q, A, W.x0, W.y0, odd ? b1 : b0, odd ? b0 : b1, L);
+    const T* const in = odd ? b1 : b0;
+    T* const out = odd ? b0 : b1;
+    if constexpr (PER == kMixedForms) {
+        switch (W.form) {
+            case 0: fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, 0>(C, Q, A, W.x0, W.y0, in, out, L); break;
+            case 1: fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, 1>(C, Q, A, W.x0, W.y0, in, out, L); break;
+            default: fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, 2>(C, Q, A, W.x0, W.y0, in, out, L);
+        }
+    } else {
+        fused2d_tile<T, S, NDMI, TX, TY, NT, SOLVER_DEPONDT, PER>(C, Q, A, W.x0, W.y0, in, out, L);
+    }
 }
 
 // Resident replicas: one workgroup holds a whole LX x LY replica (sides powers
