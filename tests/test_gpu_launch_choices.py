@@ -4,6 +4,7 @@ cannot take the other one, with room for the spread of short timings."""
 
 import time
 
+import numpy as np
 import pytest
 
 import spin_inputs as si
@@ -62,3 +63,34 @@ def test_mixed_batch_steps_in_one_launch():
     mixed = [si.square(128, 128), si.square(96, 80), si.square(75, 70, periodic=(0, 1, 0))]
     alike = [si.square(128, 128, periodic=(0, 1, 0)), si.square(96, 80, periodic=(0, 1, 0)), mixed[2]]
     assert _batch_time(mixed) < 1.6 * _batch_time(alike)
+
+
+def test_replicas_of_a_mixed_batch_equal_single_engines():
+    """Tiled replicas of all three boundary forms, bit for bit their
+    single-engine runs on the batch's tile configuration."""
+    import paper_1901_11350_amd as pk
+
+    announce("mixed batch bits")
+    geos = [si.square(128, 64), si.square(96, 80), si.square(75, 70, periodic=(0, 1, 0)), si.square(256, 128)]
+    b = pk.Batch(0)
+    b.set_chunk(4)
+    inits = []
+    for r, geo in enumerate(geos):
+        e = pk.Engine(0, "f32")
+        e.set_geometry(geo)
+        e.set_hamiltonian(HAM_SQ)
+        inits.append(si.uniform_sphere(e.N, 70 + r))
+        e.set_spins(inits[r])
+        b.add(e, 0.3, 0.001, T=20.0, seed=5, replica=r)
+        e.close()
+    b.run(9)
+    for r, geo in enumerate(geos):
+        e = pk.Engine(0, "f32")
+        e.set_geometry(geo)
+        e.set_hamiltonian(HAM_SQ)
+        e.step_path = "shape2d/32x16x512"
+        e.set_spins(inits[r])
+        e.run(0.3, 0.001, 9, T=20.0, seed=5, replica=r)
+        assert np.array_equal(b.get_spins(r), e.get_spins()), f"replica {r}"
+        e.close()
+    b.close()
