@@ -1587,7 +1587,12 @@ void launch_shape3(sp_engine* e, const sp_llg_params* p, uint64_t step, const vo
 // (kernels_resident.hpp): beyond, the tile kernels spread the sites over more
 // CUs for less than the launch costs.
 bool resident_fits(const sp_engine* e) {
-    return e->shape >= 0 && e->N <= (e->precision == SP_F64 ? sp::resident_sites<double>() : sp::resident_sites<float>());
+    if (e->shape < 0 || e->N > (e->precision == SP_F64 ? sp::resident_sites<double>() : sp::resident_sites<float>()))
+        return false;
+    // single steps have to be shared out (rows so long that a span's
+    // neighbours are more than a workgroup's: 340 x 6 sites 9.0 us in one
+    // workgroup, 5.3 on tiles)
+    return sp::resident_window(e->R, e->geo.n[0], e->N) <= 1024;
 }
 bool resident_ok(const sp_engine* e) {
     return resident_fits(e) && !e->path_chosen && std::strcmp(e->path, "shape2d") == 0;
@@ -1599,10 +1604,15 @@ template <typename T, int S, int SOLVER>
 void go_resident(sp_engine* e, const sp_llg_params* p, uint64_t step, const void* nin, void* nout, int n_steps) {
     auto go = [&](auto ndmi, auto pt) {
         constexpr int PT = decltype(pt)::value;
-        const dim3 block((unsigned)((e->N + 64 * PT - 1) / (64 * PT) * 64));
-        hipLaunchKernelGGL((sp::k_resident2d<T, S, decltype(ndmi)::value, SOLVER, PT>), dim3(1), block, 0, e->stream,
-                           step_coef_for<T, S>(e), make_site2d<T>(e, p), make_llg<T>(p, step, p->replica), e->d_flag,
-                           static_cast<const T*>(nin), static_cast<T*>(nout), n_steps);
+        // a single step is shared out (a run goes in place, in one workgroup)
+        const int window = sp::resident_window(sp::ShapeTab<S>::R, e->geo.n[0], e->N);
+        const bool shared = n_steps == 1 && nin != nout;
+        const int groups = shared ? (e->N + sp::kResidentSpan - 1) / sp::kResidentSpan : 1;
+        const int threads = groups > 1 ? (window + 63) / 64 * 64 : (e->N + 64 * PT - 1) / (64 * PT) * 64;
+        hipLaunchKernelGGL((sp::k_resident2d<T, S, decltype(ndmi)::value, SOLVER, PT>), dim3((unsigned)groups),
+                           dim3((unsigned)threads), 0, e->stream, step_coef_for<T, S>(e), make_site2d<T>(e, p),
+                           make_llg<T>(p, step, p->replica), e->d_flag, static_cast<const T*>(nin), static_cast<T*>(nout),
+                           n_steps);
     };
     constexpr std::integral_constant<int, sp::ShapeTab<S>::NB0> dmi{};
     constexpr std::integral_constant<int, 0> none{};
@@ -2033,7 +2043,9 @@ int run_impl(sp_engine* e, const sp_llg_params* p, int64_t n_steps, int64_t obse
     for (int64_t r = 0; resident && r < n_steps;) {
         int64_t chunk = observe_every > 0 ? observe_every - r % observe_every : n_steps - r;
         chunk = std::min<int64_t>(std::min<int64_t>(chunk, n_steps - r), kResidentMaxChunk);
-        if ((rc = launch_resident<T>(e, p, e->step, e->d_n, e->d_n, (int)chunk))) return rc;
+        // a run of one step goes to the other buffer, as single steps do
+        if ((rc = launch_resident<T>(e, p, e->step, e->d_n, n_steps == 1 ? e->d_n2 : e->d_n, (int)chunk))) return rc;
+        if (n_steps == 1) std::swap(e->d_n, e->d_n2);
         e->step += (uint64_t)chunk;
         r += chunk;
         if (observe_every > 0 && r % observe_every == 0) {

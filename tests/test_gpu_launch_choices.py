@@ -94,3 +94,28 @@ def test_replicas_of_a_mixed_batch_equal_single_engines():
         assert np.array_equal(b.get_spins(r), e.get_spins()), f"replica {r}"
         e.close()
     b.close()
+
+
+@pytest.mark.parametrize("case", ["square45x45", "tri64x32", "tri32x32"])
+def test_single_steps_of_small_lattices_cost_no_more_than_a_tile_launch(case):
+    """One call of llg_step on the path the engine chose itself against the
+    tile kernel chosen by name (one workgroup for all sites took 1.2 to 1.4
+    times as long on the larger two)."""
+    import paper_1901_11350_amd as pk
+
+    announce(f"single steps {case}")
+    geo, ham = {"square45x45": (si.square(45, 45), HAM_TRI), "tri64x32": (si.triangular(64, 32), HAM_TRI),
+                "tri32x32": (si.triangular(32, 32), HAM_TRI)}[case]
+    e = pk.Engine(0, "f32")
+    e.set_geometry(geo)
+    e.set_hamiltonian(ham)
+    e.set_spins(si.uniform_sphere(e.N, 1))
+
+    def step():
+        e.llg_step(0.1, 0.0005)
+        e.synchronize()
+
+    own = _best(step, inner=30)
+    e.step_path = e.step_path
+    tile = _best(step, inner=30)
+    assert own < 1.12 * tile
