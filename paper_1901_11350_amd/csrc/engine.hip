@@ -663,13 +663,44 @@ int launch_dipole(sp_engine* e, const void* n, void* gdd) {
 }
 
 // ------------------------------------------------ general path on LDS tiles
+// Whether the tiles take less time than the site loop: the loop's time goes
+// with the bonds, the tiles' with the staged cells and, as a thread walks the
+// atoms of its cell one after another, with the atoms per cell; small lattices
+// wait on one site's chain, large ones on throughput.  us of one step stage,
+// fitted to 850 timed pairs of the two (lattices of 400 to 10^6 sites in one
+// to three dimensions, 0 to 40 bonds per atom, reach 1 to 9, 1 to 8 atoms per
+// cell, with and without DMI; within 10 %).  Per cell of one atom the line
+// lies at 5 to 6 bonds in 1D and 2D (1024^2 sites, FP32: 4 bonds 18.4 in the
+// loop and 19.9 on tiles, 8 bonds 25.1 and 19.8), at 8 for nearest neighbours
+// in 3D (100^3: 6 bonds 21.3 and 24.5, 10 bonds 28.1 and 25.0) and at 12 for a
+// reach of two there; at 16^3 cells of four atoms near 30 (12: 9.9 and 13.8).
+// The loop is left only for a gain of a twentieth.
+// Frames of which a CU holds one or two go in rounds (six atoms, reach two, 40
+// bonds on 40^3 cells: 300 tiles one per CU 65 us, 250 tiles 30).
+//   n, cells: millions of sites, of cells covered by the tiles; atoms per
+//   cell; bonds, dmi: per atom; staged: cells staged per cell of a tile;
+//   groups: workgroups a CU's LDS holds
+template <typename T>
+bool pair_tiles_pay(double n, double cells, double atoms, double bonds, double dmi, double staged, double groups) {
+    constexpr bool F = sizeof(T) == 4;
+    const double chain = F ? 4.03 + atoms * (0.89 + 0.284 * staged + 0.052 * bonds + 0.089 * dmi)
+                           : 4.42 + atoms * (0.86 + 0.315 * staged + 0.041 * bonds + 0.114 * dmi);
+    const double rounds = groups <= 2.0 ? std::ceil(cells * 1e6 / (256.0 * sp::kPairCells * groups) - 1e-6) : 1.0;
+    const double tiles = std::max(rounds * chain,
+                                  chain + cells * atoms * (F ? 11.1 + 1.89 * staged : 20.2 + 3.22 * staged));
+    const double loop = F ? 3.64 + 0.50 * bonds + n * (7.97 + 0.955 * bonds + 1.375 * (atoms - 1))
+                          : 3.94 + 0.525 * bonds + n * (14.9 + 2.435 * bonds + 1.82 * (atoms - 1));
+    return tiles < 0.95 * loop;
+}
+
 // Plans the tiles of kernels_pairs.hpp for the engine's bond table and
 // uploads its records.  Of the power-of-two shapes of 256 cells the one with
 // the least estimated work is taken: about 25 instructions per staged cell
 // and 5 per bond and site (7 where rows of eight cells meet in the LDS banks),
-// times the workgroups that LDS leaves short of four per CU.  The form is left to the site loop when no frame fits, or when
-// staging would move more cells than the bonds read (a few bonds of long
-// reach).
+// times the tiles per CU and the workgroups that LDS (frame and records) leaves
+// short of four per CU.  The site loop stays when no frame fits, when staging
+// would move more cells than the bonds read (a few bonds of long reach), and
+// where pair_tiles_pay does not say otherwise.
 constexpr int kPairLds = 158 * 1024;   // LDS of a workgroup at most
 
 template <typename T>
@@ -701,22 +732,37 @@ int pair_setup(sp_engine* e) {
         }
     }
     start[nb] = (int)bonds.size();
+    size_t lists = 0;      // bytes of the records
+    double dmi = 0.0;
+    for (int beta = 0; beta < nb; ++beta) {
+        size_t nj = 0, nd = 0;
+        for (int q = start[beta]; q < start[beta + 1]; ++q) {
+            const HostBond& b = bonds[q];
+            nj += b.J != 0.0;
+            nd += b.D[0] != 0.0 || b.D[1] != 0.0 || b.D[2] != 0.0;
+        }
+        lists += (nj + 7) / 8 * 8 * sizeof(sp::PairJ<T>) + (nd + 3) / 4 * 4 * sizeof(sp::PairD<T>);
+        dmi += (double)nd;
+    }
     sp::PairTile best{};
+    double best_groups = 0.0;
     double best_cost = 0.0;
     for (int lx = 3; lx <= 8; ++lx)
         for (int ly = 0; lx + ly <= 8; ++ly) {
             const int lz = 8 - lx - ly;
             const long long W = (1 << lx) + 2LL * reach[0], H = (1 << ly) + 2LL * reach[1], D = (1 << lz) + 2LL * reach[2];
-            const double bytes = (double)W * H * D * nb * sizeof(sp::V4<T>);
-            if (bytes > 140.0 * 1024) continue;
+            const double frame = (double)W * H * D * nb * sizeof(sp::V4<T>), bytes = frame + (double)lists;
+            if (frame > 140.0 * 1024 || bytes > kPairLds) continue;
             const long long nx = (g.n[0] + (1LL << lx) - 1) >> lx, ny = (g.n[1] + (1LL << ly) - 1) >> ly,
                             nz = (g.n[2] + (1LL << lz) - 1) >> lz;
             if (nx * ny * nz > (1LL << 30)) continue;
             const double groups = std::floor(160.0 * 1024 / bytes);
-            const double cost = (double)(nx * ny * nz) * (25.0 * W * H * D * nb + (lx == 3 ? 7.0 : 5.0) * sp::kPairCells * (double)bonds.size()) *
+            const double cost = std::ceil((double)(nx * ny * nz) / 256.0) *
+                                (25.0 * W * H * D * nb + (lx == 3 ? 7.0 : 5.0) * sp::kPairCells * (double)bonds.size()) *
                                 std::max(1.0, 4.0 / groups);
             if (best_cost > 0.0 && cost >= best_cost) continue;
             best_cost = cost;
+            best_groups = groups;
             best = sp::PairTile{};
             best.log_tx = lx;
             best.log_ty = ly;
@@ -731,7 +777,10 @@ int pair_setup(sp_engine* e) {
             best.ny = (int)ny;
             best.nz = (int)nz;
         }
-    if (best_cost == 0.0 || (double)best.PN * nb > 128.0 * (double)bonds.size() + 2048.0) return SP_OK;
+    if (best_cost == 0.0 || (double)best.PN * nb > 128.0 * (double)bonds.size() + 2048.0 ||
+        !pair_tiles_pay<T>(1e-6 * e->N, 1e-6 * sp::kPairCells * best.nx * best.ny * best.nz, nb, (double)bonds.size() / nb,
+                           dmi / nb, (double)best.PN / sp::kPairCells, best_groups))
+        return SP_OK;
     auto magic = [](int x) { return (uint32_t)(((1ull << 32) + (uint64_t)x - 1) / (uint64_t)x); };
     best.magic_PN = magic(best.PN);
     best.magic_WH = magic(best.W * best.H);
@@ -763,7 +812,6 @@ int pair_setup(sp_engine* e) {
     if (db) std::memcpy(both.data() + jb, D.data(), db);
     if (jb + db) HIPCHK(e, hipMemcpy(e->d_pairs, both.data(), jb + db, hipMemcpyHostToDevice));
     const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>) + jb + db);
-    if (bytes > kPairLds) return SP_OK;
     if (bytes > 48 * 1024) {
         // the limit belongs to the kernels, which every engine launches with
         // LDS of its own size: always the largest

@@ -119,3 +119,25 @@ def test_single_steps_of_small_lattices_cost_no_more_than_a_tile_launch(case):
     e.step_path = e.step_path
     tile = _best(step, inner=30)
     assert own < 1.12 * tile
+
+
+def test_few_bonds_are_not_summed_on_tiles():
+    """Six bonds of two cells' length per site (100^3, FP32), where staging the
+    halo costs more than the loop over the bonds, against the same table with
+    one pair too far for any frame, which only the loop takes: the smaller
+    table is the faster one (on tiles it took 1.25 times as long)."""
+    import paper_1901_11350_amd as pk
+
+    announce("few bonds")
+    pairs = [(0, 0, d, 0.5, (0.0, 0.0, 0.0)) for d in ((2, 0, 0), (0, 2, 0), (0, 0, 2))]
+    times = []
+    for extra in ([], [(0, 0, (40, 40, 40), 0.5, (0.0, 0.0, 0.0))]):
+        e = pk.Engine(0, "f32")
+        e.set_geometry(si.simple_cubic(100, 100, 100))
+        e.set_hamiltonian(si.Hamiltonian(mu=(2.0,), B=(0, 0, 0.3), K=(0.1,), K_axis=((0, 0, 1),)))
+        e.set_pairs(pairs + extra)
+        e.set_spins(si.uniform_sphere(e.N, 1))
+        e.step_path = "twopass"
+        times.append(_best(lambda: e.run(0.3, 0.001, 50), repeats=5))
+        e.close()
+    assert times[0] < 1.05 * times[1]
