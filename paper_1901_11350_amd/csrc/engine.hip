@@ -564,6 +564,14 @@ bool dipole_mfma_plan(const sp_engine* e, sp::DipoleMfmaArgs<T>& a, int& wa) {
 // Slices of partial sums the direct sum writes.
 int dipole_slices(const sp_engine* e) { return e->dd_table ? std::max(e->dd_slices, e->dd_mslices) : e->dd_slices; }
 
+sp::DipoleGeo dipole_geo(const sp_engine* e) {
+    const HostGeo& g = e->geo;
+    sp::DipoleGeo o{};
+    for (int k = 0; k < 9; ++k) o.v[k] = g.bravais[k] * g.a;
+    for (int k = 0; k < 3 * g.nb; ++k) o.v[9 + k] = g.basis[k] * g.a;
+    return o;
+}
+
 // Tabulates the interaction of the matrix-core form if the lattice takes it
 // (otherwise the engine has no table and sums on the vector ALUs).
 template <typename T>
@@ -575,25 +583,11 @@ int dipole_table_setup(sp_engine* e) {
     if (!dipole_mfma_plan<T>(e, a, wa)) return SP_OK;
     const HostGeo& g = e->geo;
     const int noff = (2 * g.n[2] - 1) * g.nb * g.nb;
-    std::vector<double> geo(9 + 3 * (size_t)g.nb);
-    for (int k = 0; k < 9; ++k) geo[k] = g.bravais[k] * g.a;
-    for (int b = 0; b < g.nb; ++b)
-        for (int k = 0; k < 3; ++k) geo[9 + 3 * b + k] = g.basis[3 * b + k] * g.a;
-    double* d_geo = nullptr;
-    int rc = dalloc(e, d_geo, geo.size() * sizeof(double));
-    if (rc) return rc;
-    if (dalloc(e, e->dd_table, (size_t)noff * (2 * a.Nb - 1) * 6 * a.RL * sizeof(T))) {
-        (void)hipFree(d_geo);
+    if (dalloc(e, e->dd_table, (size_t)noff * (2 * a.Nb - 1) * 6 * a.RL * sizeof(T)))
         return SP_OK;      // no room for the table: the vector form
-    }
-    hipError_t st = hipMemcpy(d_geo, geo.data(), geo.size() * sizeof(double), hipMemcpyHostToDevice);
-    if (st == hipSuccess) {
-        hipLaunchKernelGGL((sp::k_dipole_table<T>), dim3(blocks_for(a.RL), (unsigned)(2 * a.Nb - 1), (unsigned)noff),
-                           dim3(256), 0, e->stream, a, d_geo, static_cast<T*>(e->dd_table));
-        st = hipGetLastError();
-    }
-    if (st == hipSuccess) st = hipStreamSynchronize(e->stream);
-    (void)hipFree(d_geo);
+    hipLaunchKernelGGL((sp::k_dipole_table<T>), dim3(blocks_for(a.RL), (unsigned)(2 * a.Nb - 1), (unsigned)noff),
+                       dim3(256), 0, e->stream, a, dipole_geo(e), static_cast<T*>(e->dd_table));
+    const hipError_t st = hipGetLastError();
     if (st != hipSuccess) return fail(e, SP_E_HIP, std::string("dipole table: ") + hipGetErrorString(st));
     e->dd_mslices = a.slices;
     return SP_OK;

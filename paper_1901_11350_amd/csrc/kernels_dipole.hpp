@@ -20,6 +20,12 @@
 
 namespace sp {
 
+// Lattice of an interaction table: A1, A2, A3, then the basis (Angstrom).
+// Small enough to travel with a launch's arguments.
+struct DipoleGeo {
+    double v[9 + 3 * kMaxBasis];
+};
+
 template <typename T>
 struct DipoleArgs {
     int N;
@@ -170,10 +176,9 @@ constexpr int kDipChunk = 64;       // source sites of a row per unit
 // Interaction table [offset][db + Nb - 1][component][RL]: component xx xy xz
 // yy yz zz of (1 - 3 r^ r^) / r^3 with r the translation (da, db, c' - c)
 // plus the basis difference; zero at r = 0 and beyond the sample.
-// geo as in the FFT form: A1, A2, A3, then the basis (Angstrom).
 template <typename T>
-__global__ void __launch_bounds__(256) k_dipole_table(DipoleMfmaArgs<T> a, const double* __restrict__ geo,
-                                                      T* __restrict__ K) {
+__global__ void __launch_bounds__(256) k_dipole_table(DipoleMfmaArgs<T> a, DipoleGeo G, T* __restrict__ K) {
+    const double* geo = G.v;
     const int x = blockIdx.x * 256 + threadIdx.x;
     if (x >= a.RL) return;
     const int db = (int)blockIdx.y - (a.Nb - 1), off = blockIdx.z;

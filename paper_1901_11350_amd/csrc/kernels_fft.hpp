@@ -32,6 +32,7 @@
 // three 17; a Depondt step 117 us, now 34.7.
 #pragma once
 
+#include "kernels_dipole.hpp"
 #include "kernels_field.hpp"
 
 namespace sp {
@@ -157,9 +158,9 @@ __device__ __forceinline__ void wave_fft(Cx<T>* line, const Cx<T>* tw, int l, LD
 // Component s (xx xy xz yy yz zz) of the kernel tensor of plane-pair offset
 // `off` at grid point (ia, ib), which holds the translation (da, db) =
 // (a_i - a_j, b_i - b_j) with da = ia or ia - La.
-// geo: A1[3], A2[3], A3[3] (Angstrom), then basis[3 * Nbas] (Angstrom).
-__device__ __forceinline__ double dd_kernel_value(const FftDims& d, const double* __restrict__ geo, int off, int s,
-                                                  int ia, int ib) {
+__device__ __forceinline__ double dd_kernel_value(const FftDims& d, const DipoleGeo& G, int off, int s, int ia,
+                                                  int ib) {
+    const double* geo = G.v;
     const int nb2 = d.Nbas * d.Nbas;
     const int dc = off / nb2;                   // c' - c >= 0
     const int beta = (off % nb2) / d.Nbas, beta2 = off % d.Nbas;
@@ -190,8 +191,7 @@ __device__ __forceinline__ double dd_kernel_value(const FftDims& d, const double
 template <typename T, int LOGL, bool KERNEL>
 __global__ void __launch_bounds__((FftLine<T, LOGL>::NT))
     k_dd_rows(FftDims d, int channels, int rows, long long ka_pitch, long long ch_pitch, const T* __restrict__ n,
-              const T* __restrict__ mu_plane, const double* __restrict__ geo, const Cx<T>* __restrict__ tw,
-              Cx<T>* __restrict__ X) {
+              const T* __restrict__ mu_plane, DipoleGeo geo, const Cx<T>* __restrict__ tw, Cx<T>* __restrict__ X) {
     using F = FftLine<T, LOGL>;
     constexpr int L = F::L, NT = F::NT;
     __shared__ Cx<T> buf[F::ROWS * F::PITCH];
