@@ -80,16 +80,15 @@ __device__ __forceinline__ V3<T> mc_trial(V3<T> n, const T u[3], T cos_cone) {
 }
 
 // Exchange and DMI sums of the site (a, b, c), its bonds q0 to q1 - 1 uniform
-// over the workgroup, in the order of site_terms.  Six bonds at a time: their
+// over the workgroup, in the order of site_terms.  G bonds at a time: their
 // records are read together (scalar), then their neighbours, then their
 // couplings under the neighbours' latency.  NEAR: no offset reaches past one
 // lattice length of a periodic axis, so a wrap is two selects; with the
 // division of the general case in the loop its branches kept every record's
 // load behind the one before (6.9 -> 6.0 us per colour of 30^3 sites).  DMI: the vectors are read.
-template <typename T, bool NEAR, bool DMI>
+template <typename T, bool NEAR, bool DMI, int G>
 __device__ __forceinline__ void mc_pair_sums(const Lattice& L, const BondCoef<double>& C, const T* __restrict__ n, int a,
                                              int b, int c, int q0, int q1, int i, V3<double>& gj, V3<double>& gd) {
-    constexpr int G = 6;
     auto coord = [](int t, int len, int per, bool& ok) {
         if constexpr (!NEAR) return frame_coord(t, len, per, ok);
         const int w = t < 0 ? t + len : (t >= len ? t - len : t);
@@ -128,9 +127,17 @@ __device__ __forceinline__ void mc_pair_terms(const Lattice& L, const BondCoef<d
                                               int b, int c, int q0, int q1, int i, bool near, bool dmi, V3<double>& gj,
                                               V3<double>& gd) {
     gj = gd = V3<double>{0.0, 0.0, 0.0};
-    if (!near) mc_pair_sums<T, false, true>(L, C, n, a, b, c, q0, q1, i, gj, gd);
-    else if (dmi) mc_pair_sums<T, true, true>(L, C, n, a, b, c, q0, q1, i, gj, gd);
-    else mc_pair_sums<T, true, false>(L, C, n, a, b, c, q0, q1, i, gj, gd);
+    // six at a time, or four where that leaves fewer places empty: a launch of
+    // few sites is one wavefront's chain, and an empty place costs it as much
+    // as a bond (64 sites of four bonds, 100 sweeps: 1351 us by sixes, 1264 by
+    // fours; 1024^2 sites, 20 sweeps: 885 and 819)
+    const int count = q1 - q0;
+    const bool four = (count + 3) / 4 * 4 < (count + 5) / 6 * 6;
+    if (!near) mc_pair_sums<T, false, true, 6>(L, C, n, a, b, c, q0, q1, i, gj, gd);
+    else if (dmi && four) mc_pair_sums<T, true, true, 4>(L, C, n, a, b, c, q0, q1, i, gj, gd);
+    else if (dmi) mc_pair_sums<T, true, true, 6>(L, C, n, a, b, c, q0, q1, i, gj, gd);
+    else if (four) mc_pair_sums<T, true, false, 4>(L, C, n, a, b, c, q0, q1, i, gj, gd);
+    else mc_pair_sums<T, true, false, 6>(L, C, n, a, b, c, q0, q1, i, gj, gd);
 }
 
 // One colour of one sweep: a workgroup takes sites of one class of the
