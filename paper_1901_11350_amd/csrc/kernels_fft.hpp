@@ -7,29 +7,36 @@
 //   g_i = C_dd mu_i sum_{p'} sum_{a', b'} W_{p p'}(a - a', b - b') mu_{p'} n_{p'}(a', b')
 // is, for every plane pair, a 2D linear convolution with the symmetric
 // tensor W = (1 - 3 r^ r^) / r^3 (W = 0 for i = j).  Zero padding to
-// La >= 2 Na - 1, Lb >= 2 Nb - 1 (powers of two, at least 32) makes the
-// circular convolution of the FFT equal to the linear one: only pairs inside
-// the sample interact, exactly as in the direct sum.
+// La >= 2 Na - 1, Lb >= 2 Nb - 1 (powers of two) makes the circular
+// convolution of the FFT equal to the linear one: only pairs inside the
+// sample interact, exactly as in the direct sum.
 //
 // The 3P channels (component x plane) are real, so only the frequencies
-// ka = 0 .. La/2 are kept.  Per evaluation three kernels:
-//   k_dd_rows   two real rows (channels 2q, 2q + 1) as one complex line,
-//               transformed along a and split into the two half spectra;
-//   k_dd_cols   one workgroup per ka holds the columns of all channels in
-//               LDS: transform along b, P x P plane-pair product with the
-//               kernel spectra per frequency, transform back;
-//   k_dd_out    half spectra of two channels recombined, transformed back
-//               along a, scaled and written as rows of the gradient.
-// Between them the half spectra lie as [ka][channel][b], so that the columns
-// of one ka are contiguous; a workgroup of the row kernels takes rows side
-// by side and moves them as 64-byte segments.
+// ka = 0 .. La/2 are kept, and two channels 2q, 2q + 1 go along a as one
+// complex line, which is split into the two half spectra.  Two forms:
+//   fused (up to four planes, lines of 32 points and more), half spectra as
+//   [ka][b][channel]:
+//     k_dd_row    one workgroup per row b, all its lines in LDS: spins to
+//                 half spectra;
+//     k_dd_cols   one workgroup per ka, the columns of all channels in LDS:
+//                 transform along b, P x P plane-pair product with the kernel
+//                 spectra per frequency, transform back;
+//     k_dd_row    half spectra to rows of the gradient, or, in a step, through
+//                 the step's stage to the half spectra of the new spins;
+//   separate (lines of 4 points and more; an axis of one cell is not
+//   transformed), half spectra as [channel][ka][b]:
+//     k_dd_rows   rows of two channels, several rows side by side (64-byte
+//                 segments);
+//     k_dd_lines  columns, k_dd_mix the plane-pair product with one thread per
+//                 channel and frequency, k_dd_lines back;
+//     k_dd_out    half spectra of two channels to rows of the gradient.
 //
 // What bounds it: on the 128x128x4 film the arrays (1.6 MB of half spectra,
-// 11 MB of kernel spectra) stay in L2, and the time is launches and the
+// 6.3 MB of kernel spectra) stay in L2, and the time is launches and the
 // latency of load, transform, store in each.  Eight launches with every
 // transform stage between workgroup barriers and the full spectra of every
-// channel passing through memory between them took 49 us per field, these
-// three 17; a Depondt step 117 us, now 34.7.
+// channel passing through memory between them took 49 us per field, the three
+// of the fused form 17; a Depondt step 117 us, now 34.7.
 #pragma once
 
 #include "kernels_dipole.hpp"

@@ -35,8 +35,9 @@ __device__ __forceinline__ double lane_of(double v, int lane) {
 // Butterfly over the 64 lanes (all active): neighbours, pairs, quads and
 // eights through DPP (quad permutes, then mirrors, whose partner holds the
 // same partial as the butterfly's), the four rows of 16 through scalar
-// reads.  The order of the additions is that of six exchanges through LDS,
-// each of which waited on the one before.
+// reads.  Six exchanges through LDS, each of which waited on the one before,
+// took the distances from 32 down to 1, these from 1 up: the same sum in
+// another order of additions, equal to its last bit or two.
 __device__ __forceinline__ double wave_sum(double v) {
     v += dpp<0xB1>(v);      // lane ^ 1
     v += dpp<0x4E>(v);      // lane ^ 2
