@@ -314,16 +314,16 @@ __device__ __forceinline__ V3<T> shape_B_aos(const StepCoef<T>& C, const Site2D<
     return B;
 }
 
-// shape_B_aos with the neighbours' cells given (nb[q]).
-template <typename T, int S, int NDMI>
-__device__ __forceinline__ V3<T> shape_B_cells(const StepCoef<T>& C, const Site2D<T>& Q, const V4<T>* sv,
-                                               const int (&nb)[ShapeTab<S>::NB], V3<T> ni, V3<T> base) {
+// The field of one site from its neighbours' cells, cell(q) giving bond q's.
+template <typename T, int S, int NDMI, typename Cell>
+__device__ __forceinline__ V3<T> shape_B_of(const StepCoef<T>& C, const Site2D<T>& Q, Cell cell, V3<T> ni,
+                                            V3<T> base) {
     using SH = ShapeTab<S>;
     V3<T> acc[SH::NS];
     V3<T> B = base;
 #pragma unroll
     for (int q = 0; q < SH::NB; ++q) {
-        const V3<T> nj = lds_cell_xyz(sv, nb[q]);
+        const V3<T> nj = cell(q);
         const int sh = SH::sh[q];
         if (first_of_shell<SH>(q)) acc[sh] = nj;
         else acc[sh] = acc[sh] + nj;
@@ -345,6 +345,13 @@ __device__ __forceinline__ V3<T> shape_B_cells(const StepCoef<T>& C, const Site2
         B.z += C.J[s] * acc[s].z;
     }
     return B;
+}
+
+// shape_B_of with the neighbours' cells by index (nb[q]).
+template <typename T, int S, int NDMI>
+__device__ __forceinline__ V3<T> shape_B_cells(const StepCoef<T>& C, const Site2D<T>& Q, const V4<T>* sv,
+                                               const int (&nb)[ShapeTab<S>::NB], V3<T> ni, V3<T> base) {
+    return shape_B_of<T, S, NDMI>(C, Q, [&](int q) { return lds_cell_xyz(sv, nb[q]); }, ni, base);
 }
 
 struct TileMap {
@@ -710,10 +717,21 @@ __global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, 
 // Resident replicas: one workgroup holds a whole LX x LY replica (sides powers
 // of two) in LDS, as 16-byte cells, and advances it n_steps Depondt steps
 // without touching HBM in between.  Each thread owns the sites tid + j*NT and
-// keeps their spin, rotation vector w and thermal field in registers;
-// neighbours wrap by a mask (a zero cell past open edges), so a step has two
-// barriers and no frame of images to refresh (which took two more and a
-// third of the step: 2.9 us for 32^2, 9.1 us for 64^2).
+// keeps their spin, rotation vector w and thermal field in registers.  The
+// cells lie in a frame of zero cells as wide as the stencil, which open edges
+// read; neighbours past periodic edges are read from the other side, so a
+// step has two barriers and no images to refresh.
+//
+// What bounds it is the instructions of one CU (and, with four sites a thread,
+// the 128 registers of a 1024-thread workgroup), so a neighbour should cost no
+// more than its read: the cell is one of 2R+1 columns, wrapped once per launch,
+// plus a constant, as a thread's rows lie NT/LX apart and only those of the
+// first and the last can leave the lattice; theirs add a row offset that is
+// the same for a whole wavefront of LX = 64.  Wrapping each neighbour's index
+// by masks, with tests for open edges, took 13.5 us a step for 64^2 with the
+// 18 bonds of three triangular shells and DMI (81 registers spilled), this
+// 7.3 us (18 bonds, 32^2: 2.03 and 1.92; four bonds: 3.80 and 3.90 for 64^2,
+// 1.10 and 1.14 for 32^2).
 template <typename T, int S, int NDMI, int LX, int LY, int NT>
 __global__ void __launch_bounds__(NT) k_batch_resident(StepCoef<T> C, Site2D<T> Q,
                                                        const ReplicaDesc<T>* __restrict__ reps,
@@ -721,67 +739,79 @@ __global__ void __launch_bounds__(NT) k_batch_resident(StepCoef<T> C, Site2D<T> 
                                                        const unsigned long long* __restrict__ step_base,
                                                        int n_steps) {
     using SH = ShapeTab<S>;
-    constexpr int N = LX * LY, PT = (N + NT - 1) / NT;
-    static_assert(N % NT == 0, "whole sites per thread");
-    __shared__ V4<T> sN[N + 1];
-    __shared__ V4<T> sP[N + 1];
+    constexpr int N = LX * LY, PT = N / NT, RP = NT / LX, R = SH::R, W = LX + 2 * R, P = W * (LY + 2 * R);
+    static_assert(N % NT == 0 && NT % LX == 0, "whole sites per thread, whole rows between them");
+    static_assert((LX & (LX - 1)) == 0 && (LY & (LY - 1)) == 0 && RP >= R, "sides wrap by a mask");
+    __shared__ V4<T> sN[P];
+    __shared__ V4<T> sP[P];
     const ReplicaDesc<T> Rp = reps[list[blockIdx.x]];
     LLGArgs<T> A;
     const unsigned long long first = *step_base;
     replica_args(Rp, first, Q, A);
     const int tid = threadIdx.x;
     T* g = Rp.n[0];
+    for (int c = tid; c < P; c += NT) sN[c] = sP[c] = V4<T>{T(0), T(0), T(0), T(0)};
+    __syncthreads();
+    const int x = tid & (LX - 1);
+    const int y0 = LX % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / LX) : tid / LX;
+    const int c0 = (y0 + R) * W + R + x;
     V3<T> ni[PT], base[PT], keep[PT];
 #pragma unroll
     for (int j = 0; j < PT; ++j) {
-        const int s = tid + j * NT;
-        ni[j] = load3(g, N, s);
-        sN[s] = V4<T>{ni[j].x, ni[j].y, ni[j].z, T(0)};
+        ni[j] = load3(g, N, tid + j * NT);
+        sN[c0 + j * RP * W] = V4<T>{ni[j].x, ni[j].y, ni[j].z, T(0)};
     }
-    if (tid == 0) sN[N] = sP[N] = V4<T>{T(0), T(0), T(0), T(0)};
     __syncthreads();
-    const bool open_a = !Q.per_a, open_b = !Q.per_b;
-    // cells of the neighbours of site s (formed where they are used: four
-    // sites' would not stay in registers)
-    auto cells = [&](int s, int (&nb)[SH::NB]) {
-        const int x = s & (LX - 1), y = s / LX;
+    int col[2 * R + 1];            // row y0, columns x-R..x+R
 #pragma unroll
-        for (int q = 0; q < SH::NB; ++q) {
-            const int gx = x + SH::da[q], gy = y + SH::db[q];
-            nb[q] = (gx & (LX - 1)) + (gy & (LY - 1)) * LX;
-            if (open_a && (gx < 0 || gx >= LX)) nb[q] = N;
-            if (open_b && (gy < 0 || gy >= LY)) nb[q] = N;
-        }
+    for (int d = -R; d <= R; ++d) col[d + R] = c0 - x + (Q.per_a ? (x + d) & (LX - 1) : x + d);
+    int below[R], above[R];        // rows past the first and the last one, seen from row y0
+#pragma unroll
+    for (int d = 1; d <= R; ++d) {
+        const int lo = y0 - d, hi = y0 + (PT - 1) * RP + d;
+        below[d - 1] = ((Q.per_b ? lo & (LY - 1) : lo) - y0) * W;
+        above[d - 1] = ((Q.per_b ? hi & (LY - 1) : hi) - y0) * W;
+    }
+    auto cell = [&](const V4<T>* sv, int j, int q) {
+        const int da = SH::da[q], db = SH::db[q];
+        int row = (j * RP + db) * W;
+        if (j == 0 && db < 0) row = below[-db - 1];
+        if (j == PT - 1 && db > 0) row = above[db - 1];
+        return lds_cell_xyz(sv, col[da + R] + row);
     };
     const V3<T> Bext{C.Bext[0], C.Bext[1], C.Bext[2]};
     const T h = rot_half_factor(A.gp, A.dt);
     for (int k = 0; k < n_steps; ++k) {
+        // the sums of columns and rows are formed where they are used: all
+        // of them, held over the steps, spilled 38 registers with 18 bonds
+        if constexpr (LX % 64 == 0 && SH::NB > 4) {
+#pragma unroll
+            for (int d = 0; d < R; ++d) asm volatile("" : "+s"(below[d]), "+s"(above[d]));
+        }
         A.key.step_lo = (uint32_t)(first + k);
         A.key.step_hi = (uint32_t)((first + k) >> 32);
         V3<T> p[PT];
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int s = tid + j * NT;
-            int nb[SH::NB];
-            cells(s, nb);
             base[j] = Bext;
             if (A.thermal) {
                 asm volatile("");   // the draw stays behind the branch
-                base[j] = base[j] + Q.sigma * normals3(thermal_bits(A.key, (uint32_t)s), T(0));
+                base[j] = base[j] + Q.sigma * normals3(thermal_bits(A.key, (uint32_t)(tid + j * NT)), T(0));
             }
-            keep[j] = llg_w(ni[j], shape_B_cells<T, S, NDMI>(C, Q, sN, nb, ni[j], base[j]), A.alpha);
+            auto nb = [&](int q) { return cell(sN, j, q); };
+            keep[j] = llg_w(ni[j], shape_B_of<T, S, NDMI>(C, Q, nb, ni[j], base[j]), A.alpha);
             p[j] = rotate_half(ni[j], keep[j], h);
-            sP[s] = V4<T>{p[j].x, p[j].y, p[j].z, T(0)};
+            sP[c0 + j * RP * W] = V4<T>{p[j].x, p[j].y, p[j].z, T(0)};
+            __builtin_amdgcn_sched_barrier(0);   // one site's cells in registers at a time
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < PT; ++j) {
-            const int s = tid + j * NT;
-            int nb[SH::NB];
-            cells(s, nb);
-            const V3<T> wp = llg_w(p[j], shape_B_cells<T, S, NDMI>(C, Q, sP, nb, p[j], base[j]), A.alpha);
+            auto nb = [&](int q) { return cell(sP, j, q); };
+            const V3<T> wp = llg_w(p[j], shape_B_of<T, S, NDMI>(C, Q, nb, p[j], base[j]), A.alpha);
             ni[j] = renorm_if_float(rotate_half(ni[j], keep[j] + wp, T(0.5) * h));
-            sN[s] = V4<T>{ni[j].x, ni[j].y, ni[j].z, T(0)};
+            sN[c0 + j * RP * W] = V4<T>{ni[j].x, ni[j].y, ni[j].z, T(0)};
+            __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
     }
