@@ -161,7 +161,7 @@ struct sp_engine {
     // general path on LDS tiles (kernels_pairs.hpp)
     bool pair_ok = false;
     sp::PairTile ptile{};
-    void* d_pairs = nullptr;          // the exchange records, then the DMI records
+    void* d_pairs = nullptr;          // the exchange records, then the DMI records (behind d_D)
     int pair_js[sp::kMaxBasis + 1] = {}, pair_ds[sp::kMaxBasis + 1] = {};
     void* dd_table = nullptr;         // interaction table of the matrix-core direct sum, or null
     int dd_mslices = 0;               // its slices
@@ -315,10 +315,11 @@ void free_state_buffers(sp_engine* e) {
     e->mc_rows_cap = 0;
     dfree(e->d_n); dfree(e->d_n2); dfree(e->d_np); dfree(e->d_A); dfree(e->d_g);
     dfree(e->d_gdd); dfree(e->d_gddp); dfree(e->d_pos); dfree(e->d_ddpart);
-    dfree(e->dd_table); dfree(e->d_pairs);
+    dfree(e->dd_table);
     void* p = e->d_bond; dfree(p); e->d_bond = nullptr;
     p = e->d_bstart; dfree(p); e->d_bstart = nullptr;
     dfree(e->d_J); dfree(e->d_D); dfree(e->d_J64); dfree(e->d_D64);
+    e->d_pairs = nullptr;
     fft_free(e->fft);
     e->fft = nullptr;
 }
@@ -687,8 +688,9 @@ bool pair_tiles_pay(double n, double cells, double atoms, double bonds, double d
     return tiles < 0.95 * loop;
 }
 
-// Plans the tiles of kernels_pairs.hpp for the engine's bond table and
-// uploads its records.  Of the power-of-two shapes of 256 cells the one with
+// Plans the tiles of kernels_pairs.hpp for the engine's bond table and writes
+// its records, which upload_ham puts behind the bond vectors: an allocation and
+// a copy of their own cost every set_hamiltonian and destroy 60 us together.  Of the power-of-two shapes of 256 cells the one with
 // the least estimated work is taken: about 25 instructions per staged cell
 // and 5 per bond and site (7 where rows of eight cells meet in the LDS banks),
 // times the tiles per CU and the workgroups that LDS (frame and records) leaves
@@ -698,9 +700,9 @@ bool pair_tiles_pay(double n, double cells, double atoms, double bonds, double d
 constexpr int kPairLds = 158 * 1024;   // LDS of a workgroup at most
 
 template <typename T>
-int pair_setup(sp_engine* e) {
+int pair_setup(sp_engine* e, std::vector<char>& records) {
     e->pair_ok = false;
-    dfree(e->d_pairs);
+    records.clear();
     const HostGeo& g = e->geo;
     const int nb = g.nb;
     std::vector<HostBond> bonds;     // offsets of periodic axes reduced to the nearest image
@@ -799,12 +801,6 @@ int pair_setup(sp_engine* e) {
     // division of frame indices by W, W H and PN through a multiplication is
     // exact below 2^16 (140 KB of LDS hold 8,960 cells)
     const size_t jb = J.size() * sizeof(J[0]), db = D.size() * sizeof(D[0]);
-    int rc = dalloc(e, e->d_pairs, std::max<size_t>(jb + db, 64));
-    if (rc) return rc;
-    std::vector<char> both(jb + db);
-    if (jb) std::memcpy(both.data(), J.data(), jb);
-    if (db) std::memcpy(both.data() + jb, D.data(), db);
-    if (jb + db) HIPCHK(e, hipMemcpy(e->d_pairs, both.data(), jb + db, hipMemcpyHostToDevice));
     const int bytes = (int)(best.PN * nb * sizeof(sp::V4<T>) + jb + db);
     if (bytes > 48 * 1024) {
         // the limit belongs to the kernels, which every engine launches with
@@ -817,6 +813,9 @@ int pair_setup(sp_engine* e) {
                 return SP_OK;      // the site loop stays
             }
     }
+    records.resize(jb + db);
+    if (jb) std::memcpy(records.data(), J.data(), jb);
+    if (db) std::memcpy(records.data() + jb, D.data(), db);
     e->ptile = best;
     e->pair_ok = true;
     return SP_OK;
@@ -1815,7 +1814,7 @@ int copy_out_soa(sp_engine* e, double* dst, const void* src, int64_t n3) {
 }
 
 template <typename T>
-int upload_ham(sp_engine* e) {
+int upload_ham(sp_engine* e, const std::vector<char>& records) {
     const size_t nbond = e->bonds.size();
     std::vector<int4> bd(std::max<size_t>(nbond, 1));
     std::vector<T> J(std::max<size_t>(nbond, 1)), D(3 * std::max<size_t>(nbond, 1));
@@ -1829,11 +1828,16 @@ int upload_ham(sp_engine* e) {
     if ((rc = dalloc(e, e->d_bond, bd.size() * sizeof(int4)))) return rc;
     if ((rc = dalloc(e, e->d_bstart, e->bstart.size() * sizeof(int)))) return rc;
     if ((rc = dalloc(e, e->d_J, J.size() * sizeof(T)))) return rc;
-    if ((rc = dalloc(e, e->d_D, D.size() * sizeof(T)))) return rc;
+    const size_t rec_at = (D.size() * sizeof(T) + 255) / 256 * 256;
+    std::vector<char> vectors(rec_at + records.size());
+    std::memcpy(vectors.data(), D.data(), D.size() * sizeof(T));
+    if (!records.empty()) std::memcpy(vectors.data() + rec_at, records.data(), records.size());
+    if ((rc = dalloc(e, e->d_D, vectors.size()))) return rc;
+    e->d_pairs = records.empty() ? nullptr : static_cast<char*>(e->d_D) + rec_at;
     HIPCHK(e, hipMemcpy(e->d_bond, bd.data(), bd.size() * sizeof(int4), hipMemcpyHostToDevice));
     HIPCHK(e, hipMemcpy(e->d_bstart, e->bstart.data(), e->bstart.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(e, hipMemcpy(e->d_J, J.data(), J.size() * sizeof(T), hipMemcpyHostToDevice));
-    HIPCHK(e, hipMemcpy(e->d_D, D.data(), D.size() * sizeof(T), hipMemcpyHostToDevice));
+    HIPCHK(e, hipMemcpy(e->d_D, vectors.data(), vectors.size(), hipMemcpyHostToDevice));
     if constexpr (sizeof(T) == 4) {
         std::vector<double> J64(J.size()), D64(D.size());
         for (size_t q = 0; q < nbond; ++q) {
@@ -2674,12 +2678,6 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
             return rc;
         }
     }
-    if ((rc = DISPATCH(e, upload_ham, e)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
-        free_state_buffers(e);
-        e->has_ham = false;
-        e->has_spins = false;
-        return rc;
-    }
     const int rows = (int)std::min<long long>(1024, (e->N + 255) / 256);
     if (rows > e->partial_rows) {
         if ((rc = dalloc(e, e->d_partials, (size_t)rows * sp::OBS_NVALS * sizeof(double)))) return rc;
@@ -2719,7 +2717,9 @@ int install_ham(sp_engine* e, const HostHam& H, const std::vector<HostBond>& bon
     // lattices with a 2D stencil have kernels of their own for everything the
     // pair tiles do
     e->pair_ok = false;
-    if (e->shape < 0 && (rc = DISPATCH(e, pair_setup, e))) {
+    std::vector<char> records;
+    if ((e->shape < 0 && (rc = DISPATCH(e, pair_setup, e, records))) ||
+        (rc = DISPATCH(e, upload_ham, e, records)) || (H.ddi == SP_DDI_FFT && (rc = DISPATCH(e, fft_setup, e)))) {
         free_state_buffers(e);
         e->has_ham = false;
         e->has_spins = false;
