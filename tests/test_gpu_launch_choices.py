@@ -154,9 +154,10 @@ def test_pair_tiles_add_little_to_an_engine_s_setup():
 
     announce("pair tile setup")
     honey = si.honeycomb(86, 47)
-    ham = {"honeycomb": si.Hamiltonian(mu=(2.0, 2.0), B=(0, 0, 0.3), K=(0.1, 0.1), K_axis=((0, 0, 1),) * 2, J=(1.0,),
-                                       D=(0.2,)),
-           "triangular": si.Hamiltonian(mu=(2.0,), B=(0, 0, 0.3), K=(0.1,), K_axis=((0, 0, 1),), J=(1.0,), D=(0.2,))}
+    ham = {"honeycomb": si.Hamiltonian(mu=(2.0, 2.0), B=(0, 0, 0.3), K=(0.1, 0.1), K_axis=((0, 0, 1),) * 2,
+                                       J=(1.0, -0.2, -0.1), D=(0.2,)),
+           "triangular": si.Hamiltonian(mu=(2.0,), B=(0, 0, 0.3), K=(0.1,), K_axis=((0, 0, 1),),
+                                        J=(1.0, -0.2, -0.1), D=(0.2,))}
     geo = {"honeycomb": honey, "triangular": si.triangular(94, 86)}
     times = {}
     for name in ("triangular", "honeycomb"):
