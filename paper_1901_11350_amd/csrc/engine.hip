@@ -1037,7 +1037,7 @@ sp::StencilB<T> make_stencilb(const sp_engine* e, int WN, int HN, int PN, int WP
     S.nb = e->geo.nb;
     int q = 0;
     for (int beta = 0; beta < S.nb; ++beta) {
-        S.bstart[beta] = q;
+        S.bstart[beta] = S.dend[beta] = q;
         for (int k = e->bstart[beta]; k < e->bstart[beta + 1]; ++k, ++q) {
             const HostBond& b = e->bonds[k];
             S.offN[q] = PN * b.bj + b.d[0] + WN * (b.d[1] + HN * b.d[2]);
@@ -1045,7 +1045,7 @@ sp::StencilB<T> make_stencilb(const sp_engine* e, int WN, int HN, int PN, int WP
             S.J[q] = (T)b.J;
             for (int c = 0; c < 3; ++c) {
                 S.D[q][c] = (T)b.D[c];
-                if (S.D[q][c] != T(0)) S.dmi |= 1u << (q >> 2);
+                if (S.D[q][c] != T(0)) S.dend[beta] = (q / 4 + 1) * 4;
             }
         }
         for (; q % 4; ++q) {   // zero bonds (the struct is value-initialised)

@@ -40,8 +40,8 @@ constexpr int kMaxStencilB = 48;   // directed bonds of all basis atoms together
 template <typename T>
 struct StencilB {
     int nb;
-    unsigned dmi;                  // bit g: some bond of group g (bonds 4g to 4g + 3) has a DMI vector
     int bstart[kMaxBasis + 1];
+    int dend[kMaxBasis];           // end of atom beta's last group of four bonds with a DMI vector
     int offN[kMaxStencilB];
     int offP[kMaxStencilB];
     T J[kMaxStencilB];
@@ -69,57 +69,52 @@ __device__ __forceinline__ V3<T> tile_field(const StencilB<T>& S, const SiteB<T>
     g.x -= kn * Q.Kax[beta][0];
     g.y -= kn * Q.Kax[beta][1];
     g.z -= kn * Q.Kax[beta][2];
-    const int q1 = S.bstart[beta + 1];
+    const int qd = S.dend[beta], q1 = S.bstart[beta + 1];
     int q0 = S.bstart[beta];
-    if (q0 == q1) return g;
-    int o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = off[q0 + k];
-    while (true) {
-        // four full-width 16-byte reads in flight together: one empty asm
-        // keeps every padding word live (else the compiler narrows each read
-        // to 12 bytes), placed after all four so they are not serialised
+    // four full-width 16-byte reads in flight together: one empty asm keeps
+    // every padding word live (else the compiler narrows each read to 12
+    // bytes), placed after all four so they are not serialised; the
+    // coefficients' scalar loads overlap the LDS reads
+    for (; q0 < qd; q0 += 4) {
         V4<T> v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = s[c + o[k]];
-        // the coefficients' scalar loads overlap the LDS reads, as do those of
-        // the next group's offsets, which its reads would otherwise wait for;
-        // groups without DMI (the outer shells, as a rule) skip six of nine
-        // products (both: honeycomb 509 x 251, three shells, 9.03 -> 8.94 us per step)
-        T J[4];
-        const int qn = q0 + 4 < q1 ? q0 + 4 : q0;
+        for (int k = 0; k < 4; ++k) v[k] = s[c + off[q0 + k]];
+        T J[4], D[4][3];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             J[k] = S.J[q0 + k];
-            o[k] = off[qn + k];
+            D[k][0] = S.D[q0 + k][0];
+            D[k][1] = S.D[q0 + k][1];
+            D[k][2] = S.D[q0 + k][2];
         }
-        if ((S.dmi >> (q0 >> 2)) & 1u) {
-            T D[4][3];
+        if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(v[0].w), "v"(v[1].w), "v"(v[2].w), "v"(v[3].w));
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                D[k][0] = S.D[q0 + k][0];
-                D[k][1] = S.D[q0 + k][1];
-                D[k][2] = S.D[q0 + k][2];
-            }
-            if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(v[0].w), "v"(v[1].w), "v"(v[2].w), "v"(v[3].w));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const V3<T> nj{v[k].x, v[k].y, v[k].z};
-                g.x -= J[k] * nj.x + (nj.y * D[k][2] - nj.z * D[k][1]);
-                g.y -= J[k] * nj.y + (nj.z * D[k][0] - nj.x * D[k][2]);
-                g.z -= J[k] * nj.z + (nj.x * D[k][1] - nj.y * D[k][0]);
-            }
-        } else {
-            if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(v[0].w), "v"(v[1].w), "v"(v[2].w), "v"(v[3].w));
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                g.x -= J[k] * v[k].x;
-                g.y -= J[k] * v[k].y;
-                g.z -= J[k] * v[k].z;
-            }
+        for (int k = 0; k < 4; ++k) {
+            const V3<T> nj{v[k].x, v[k].y, v[k].z};
+            g.x -= J[k] * nj.x + (nj.y * D[k][2] - nj.z * D[k][1]);
+            g.y -= J[k] * nj.y + (nj.z * D[k][0] - nj.x * D[k][2]);
+            g.z -= J[k] * nj.z + (nj.x * D[k][1] - nj.y * D[k][0]);
         }
-        if (qn == q0) break;
-        q0 = qn;
+    }
+    // the groups after the last one with DMI (the outer shells, as a rule) need
+    // three of nine products; a loop of their own, as a branch per group makes
+    // the scalar loads of a group with DMI wait for it (honeycomb 256 x 256 in
+    // us per step, nine products for all / branch / two loops: three shells
+    // 7.36 / 7.27 / 6.63, one shell with DMI 6.09 / 6.39 / 6.08)
+    for (; q0 < q1; q0 += 4) {
+        V4<T> v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = s[c + off[q0 + k]];
+        T J[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) J[k] = S.J[q0 + k];
+        if constexpr (sizeof(T) == 4) asm volatile("" ::"v"(v[0].w), "v"(v[1].w), "v"(v[2].w), "v"(v[3].w));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            g.x -= J[k] * v[k].x;
+            g.y -= J[k] * v[k].y;
+            g.z -= J[k] * v[k].z;
+        }
     }
     return g;
 }
