@@ -423,7 +423,11 @@ __device__ __forceinline__ int cell_site(const Site2D<T>& Q, int x0, int y0, int
 
 // External plus thermal field of a predictor-frame cell (the base of
 // shape_B_aos): depends only on the site, the step and the seed, so it is
-// formed while the spins are still in flight.
+// formed while the spins are still in flight.  The empty asm keeps the draw
+// behind its branch: where nothing else in it needs one (periodic sides that
+// are powers of two) the compiler drew the field for every step and selected
+// afterwards, which made steps at T = 0 cost what those at T > 0 do (256 x 256,
+// three triangular shells with DMI: 5.07 us, now 4.58; at T > 0 5.24 and 5.14).
 template <typename T, int S, int TX, int TY, int PER = 0>
 __device__ __forceinline__ V3<T> cell_base(const StepCoef<T>& C, const Site2D<T>& Q, const LLGArgs<T>& A, int x0,
                                            int y0, int px, int py) {
@@ -431,6 +435,7 @@ __device__ __forceinline__ V3<T> cell_base(const StepCoef<T>& C, const Site2D<T>
     const int site = cell_site<T, S, TX, TY, PER>(Q, x0, y0, px, py, in);
     const V3<T> Bext{C.Bext[0], C.Bext[1], C.Bext[2]};
     if (!A.thermal || !in) return Bext;
+    asm volatile("");
     return Bext + Q.sigma * normals3(thermal_bits(A.key, (uint32_t)site), T(0));
 }
 
