@@ -39,16 +39,20 @@ struct U4 {
     uint32_t x, y, z, w;
 };
 
+// TRI: the three-way xors in one instruction each; without, in two.  The
+// compiler holds two more registers over the rounds with them, so a kernel
+// that spills as it is may take the plain form.
+template <bool TRI = true>
 __device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c.x;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c.z;
         U4 o;
-        // three-way xor in one instruction (truth table 0x96)
-        o.x = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c.y, k0, 0x96);
+        // (0x96: the truth table of a ^ b ^ c)
+        o.x = TRI ? __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c.y, k0, 0x96) : (uint32_t)(p1 >> 32) ^ c.y ^ k0;
         o.y = (uint32_t)p1;
-        o.z = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c.w, k1, 0x96);
+        o.z = TRI ? __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c.w, k1, 0x96) : (uint32_t)(p0 >> 32) ^ c.w ^ k1;
         o.w = (uint32_t)p0;
         c = o;
         k0 += 0x9E3779B9u;
@@ -61,8 +65,9 @@ struct ThermalKey {
     uint32_t seed_lo, seed_hi, step_lo, step_hi, replica;
 };
 
+template <bool TRI = true>
 __device__ __forceinline__ U4 thermal_bits(const ThermalKey& k, uint32_t site) {
-    return philox4x32_10(U4{site, k.step_lo, k.step_hi, k.replica}, k.seed_lo, k.seed_hi);
+    return philox4x32_10<TRI>(U4{site, k.step_lo, k.step_hi, k.replica}, k.seed_lo, k.seed_hi);
 }
 
 // Three standard normals from one Philox block: u = (x + 1/2) 2^-32, then

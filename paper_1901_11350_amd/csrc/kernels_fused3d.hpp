@@ -317,9 +317,15 @@ __global__ void __launch_bounds__(TX * TY) k_fused3d_shape(StepCoef3<T> C, Site2
         }
     };
     // thermal field of a predictor cell of plane z (in-plane offset off)
+    // FP32 instances of 26 bonds spill 25 to 46 registers; the generator's plain
+    // xors are the faster ones there (64^3 at T > 0, us per step, plain and
+    // three-way: open 25.2 and 26.2, open with bulk DMI 23.6 and 26.3, periodic
+    // 22.7 and 23.2), but not with periodic sides and DMI (23.9 and 22.9) or
+    // fewer bonds (128^3, six: 28.8 and 26.1).
+    constexpr bool kTri = sizeof(T) == 8 || ShapeTab3<S>::NB <= 18 || (PER && DK != DK_NONE);
     auto thermal = [&](bool in, long long off, long long gz) -> V3<T> {
         if (!A.thermal || !in) return V3<T>{T(0), T(0), T(0)};
-        return Q.sigma * normals3(thermal_bits(A.key, (uint32_t)(off + gz)), T(0));
+        return Q.sigma * normals3(thermal_bits<kTri>(A.key, (uint32_t)(off + gz)), T(0));
     };
     // predictor of predictor cell (px, py) of plane z into predictor slot
     // pslot(z), base the cell's external plus thermal field; returns what
