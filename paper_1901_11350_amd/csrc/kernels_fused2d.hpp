@@ -736,7 +736,10 @@ __global__ void __launch_bounds__(NT) k_batch_tiled(StepCoef<T> C, Site2D<T> Q, 
 // by masks, with tests for open edges, took 13.5 us a step for 64^2 with the
 // 18 bonds of three triangular shells and DMI (81 registers spilled), this
 // 7.3 us (18 bonds, 32^2: 2.03 and 1.92; four bonds: 3.80 and 3.90 for 64^2,
-// 1.10 and 1.14 for 32^2).
+// 1.10 and 1.14 for 32^2).  The frame of 64^2 is two cells wide for a reach of
+// one too: it leaves less of a CU's LDS than a tiled workgroup needs, which
+// beside a resident one, whose chain of steps the batch waits for, cost 1190
+// instead of 1020 us (128 steps, sides 32 to 256).
 template <typename T, int S, int NDMI, int LX, int LY, int NT>
 __global__ void __launch_bounds__(NT) k_batch_resident(StepCoef<T> C, Site2D<T> Q,
                                                        const ReplicaDesc<T>* __restrict__ reps,
@@ -744,9 +747,10 @@ __global__ void __launch_bounds__(NT) k_batch_resident(StepCoef<T> C, Site2D<T> 
                                                        const unsigned long long* __restrict__ step_base,
                                                        int n_steps) {
     using SH = ShapeTab<S>;
-    constexpr int N = LX * LY, PT = N / NT, RP = NT / LX, R = SH::R, W = LX + 2 * R, P = W * (LY + 2 * R);
+    constexpr int N = LX * LY, PT = N / NT, RP = NT / LX, R = SH::R, F = PT > 1 ? 2 : R, W = LX + 2 * F, P = W * (LY + 2 * F);
     static_assert(N % NT == 0 && NT % LX == 0, "whole sites per thread, whole rows between them");
     static_assert((LX & (LX - 1)) == 0 && (LY & (LY - 1)) == 0 && RP >= R, "sides wrap by a mask");
+    static_assert(F >= R, "a frame as wide as the reach");
     __shared__ V4<T> sN[P];
     __shared__ V4<T> sP[P];
     const ReplicaDesc<T> Rp = reps[list[blockIdx.x]];
@@ -759,7 +763,7 @@ __global__ void __launch_bounds__(NT) k_batch_resident(StepCoef<T> C, Site2D<T> 
     __syncthreads();
     const int x = tid & (LX - 1);
     const int y0 = LX % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / LX) : tid / LX;
-    const int c0 = (y0 + R) * W + R + x;
+    const int c0 = (y0 + F) * W + F + x;
     V3<T> ni[PT], base[PT], keep[PT];
 #pragma unroll
     for (int j = 0; j < PT; ++j) {

@@ -78,3 +78,25 @@ def test_four_sites_a_thread_cost_no_more_than_five_times_one(T):
         best.append(min(times))
         b.close()
     assert best[1] < 5.0 * best[0]
+
+
+def test_tiled_replicas_do_not_slow_the_resident_ones():
+    """Replicas of 32 x 32 and 64 x 64 sites with a few tiled ones beside them
+    against those alone: the resident ones bind, and take no longer (1.17
+    times as long when tiled workgroups could share their CUs)."""
+    import torch
+
+    announce("resident beside tiled")
+    ham = _ham(1, True)
+    best = []
+    for sides in ((32, 64), (32, 64, 128, 256)):
+        b, _ = _batch([(si.square(s, s), 25.0) for s in sides * 2], ham)
+        times = []
+        for _ in range(9):
+            t0 = time.perf_counter()
+            b.run(256)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        best.append(min(times))
+        b.close()
+    assert best[1] < 1.09 * best[0]
